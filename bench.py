@@ -442,7 +442,8 @@ def measure(wl, args, steps, warmup, plain_loop=True):
         vi = p.variant(dt)
         variant_name = dd.variant_names(dt)[vi] if vi >= 0 else "direct"
         kernel_name = ("direct_u8_kernel" if dt == "u8" else "direct_f32_kernel") if vi < 0 else \
-            ("u8s_kernel" if variant_name.startswith("u8s_") else "u8_kernel" if dt == "u8" else "win_kernel")
+            (("u8m_kernel" if variant_name.startswith("u8m_") else "u8s_kernel" if variant_name.startswith("u8s_") else "u8_kernel")
+             if dt == "u8" else "win_kernel")
     elif wl in ("detect_apertif", "detect_lofar"):
         # single-pulse search fused into the dedispersion epilogue (boxcar
         # widths 1..32), the unfused path (store, then search) timed beside it
@@ -475,7 +476,7 @@ def measure(wl, args, steps, warmup, plain_loop=True):
 
         def step():
             dd.detect(x, p, nsamp=b.nsamp, workspace=ws)
-        kernel_name = ("u8s_kernel" if dt == "u8" else "win_kernel") + " with the search epilogue + det_finish_kernel"
+        kernel_name = (("u8m_det_kernel" if variant_name.startswith("u8m_") else "u8s_det_kernel") if dt == "u8" else "win_kernel") + " with the search epilogue + det_finish_kernel"
     else:  # diff: forward + adjoint with the weight gradient over all beams
         w = torch.ones(beams[0].nchan, device=dev)
         p0 = plans[0]

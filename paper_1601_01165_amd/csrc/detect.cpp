@@ -36,7 +36,7 @@ static int det_variant(dedisp_plan p, bool u8) {
   if (set >= -1) return set;
   auto fits = [&](int vi) { return det_fits(p, u8, vi); };
   static const int pref_f32[] = {16, 14, 18, 13, 15, 17};
-  static const int pref_u8[] = {14, 16, 15, 12, 17, 18, 20, 13, 21, 19};
+  static const int pref_u8[] = {23, 14, 25, 27, 16, 15, 12, 17, 18, 20, 13, 21, 19, 24, 26};
   if (u8) {
     for (int vi : pref_u8)
       if (fits(vi)) return vi;

@@ -438,9 +438,6 @@ def main(out_path):
         "#pragma once\n\n",
         f"#define WIN_ACC0 {ACC0}\n\n",
         "// Table entry of one (wave tile, input row): {window start, loads, offset per row...}.\n",
-        "typedef int32_t ent4_t __attribute__((ext_vector_type(4)));\n",
-        "typedef int32_t ent8_t __attribute__((ext_vector_type(8)));\n",
-        "typedef int32_t ent16_t __attribute__((ext_vector_type(16)));\n",
         "template <int DPW> struct EntT {\n",
         "  typedef typename std::conditional<(DPW + 2 <= 4), ent4_t,\n",
         "      typename std::conditional<(DPW + 2 <= 8), ent8_t, ent16_t>::type>::type type;\n",

@@ -43,7 +43,7 @@ struct Variant {
   int nbuf;    // LDS buffers: 1 = synchronous staging, 2 = asynchronous double buffering
   int id;      // index in the variant list
   // u8 only: 0 = one LDS copy per row, int32 sums; 1 = four byte-shifted copies, packed sums (at most
-  // 256 input rows); 2 = as 1, flushed to int32 sums every 256 rows
+  // 256 input rows); 2 = as 1, flushed to int32 sums every 256 rows; 3 = four copies, summed by the matrix cores
   int mode = 0;
   // f32 only: 1 = each row's DM slots branch into static blocks of adds; the table then holds block byte
   // offsets o * (4 * tp + 4) in place of the window offsets o
@@ -137,6 +137,9 @@ struct BeamDesc {
 
 // Launchers (engine.hip).  Each returns hipSuccess or the launch error.
 hipError_t launch_tiled(const Variant& v, const TileArgs& a, int nbeam, bool adjoint, hipStream_t s);
+// uint8 variants (u8.hip); grid: tile blocks x beams.
+hipError_t launch_tiled_u8(const Variant& v, const TileArgs& a, dim3 grid, hipStream_t s);
+hipError_t launch_detect_u8(const Variant& v, const TileArgs& a, dim3 grid, hipStream_t s);
 hipError_t launch_direct_f32(const float* in, int64_t in_stride, int64_t in_beam_stride, const int32_t* delta,
                              int nchan, int ndm, const float* w, float* out, int64_t out_stride,
                              int64_t out_beam_stride, int nsamp, int nbeam, hipStream_t s);

@@ -97,7 +97,8 @@ static bool build_tables(const Variant& v, int rows_out, int rows_in, const Dela
   n_row_tiles = (rows_out + DT - 1) / DT;
   const int n_wave_tiles = n_row_tiles * NW;
   blk.assign((size_t)n_row_tiles * rows_in * 2, 0);
-  wav.assign((size_t)n_wave_tiles * rows_in * WI, 0);
+  // room for a whole pass's entries after the last row (read, not used)
+  wav.assign(((size_t)n_wave_tiles * rows_in + v.cc) * WI, 0);
   std::vector<int> stage_max(n_row_tiles, 0);
   std::atomic<int> bad(0);  // 1: window span, 2: LDS row, 3: 16-bit offset
   parallel_for(n_row_tiles, [&](int rt) {
@@ -153,7 +154,7 @@ static bool build_tables(const Variant& v, int rows_out, int rows_in, const Dela
             }
             if (v.mode == 0) {
               e[j / 2] |= (int32_t)((uint32_t)o << (16 * (j % 2)));
-            } else {
+            } else {  // modes 1 to 3
               // byte offset into the staged copies: copy o & 3, row slot c % cc, dword o >> 2
               e[j] = 4 * (((o & 3) * v.cc + c % v.cc) * (v.rowcap / 4) + (o >> 2));
             }
@@ -274,13 +275,15 @@ dedisp_status ensure_tables(dedisp_plan p, int dir, int vi, Tables** out) {
 
 // Variant preference when nothing was tuned, fastest first as measured on
 // MI355X: forward FP32 on the 1024-channel, 2048-DM beam; forward uint8 on the
-// 32-channel, 2048-DM beam; the adjoint on 32 beams of 1024 channels and
+// 32-channel, 2048-DM beam (the packed sums of variant 22 take at most 256
+// channels; past that the matrix-core shapes are 1.3 times as fast as the flushed
+// packed sums, 1.06 against 1.41 ms on 1024 channels); the adjoint on 32 beams of 1024 channels and
 // 1024 DMs.  Variants with wide register windows or int32 sums come last:
 // they fit the widest delay spans and the most channels.
 const std::vector<int>& default_order(int dir) {
   static const std::vector<int> f32 = {35, 34, 37, 38, 36, 32, 33, 22, 28, 21, 29, 31, 23, 30, 19, 20, 25, 24, 27, 26, 15, 18, 13,
                                        17, 9,  8,  16, 6,  14, 11, 7,  12, 10, 2,  3,  0,  1,  5,  4};
-  static const std::vector<int> u8 = {22, 16, 20, 15, 21, 12, 13, 17, 14, 18, 6, 2, 0, 5, 19, 9, 3, 4, 1, 8, 7, 10, 11};
+  static const std::vector<int> u8 = {22, 23, 25, 27, 26, 24, 16, 20, 15, 21, 12, 13, 17, 14, 18, 6, 2, 0, 5, 19, 9, 3, 4, 1, 8, 7, 10, 11};
   static const std::vector<int> adj = {37, 38, 26, 27, 32, 34, 35, 36, 33, 19, 21, 29, 20, 30, 9, 8, 6, 11, 12, 7, 10, 13, 22, 28,
                                        18, 15, 23, 31, 17, 16, 25, 24, 14, 2, 3, 1, 0, 5, 4};
   return dir == 1 ? u8 : dir == 2 ? adj : f32;

@@ -232,6 +232,33 @@ def test_u8_many_rows_packed_sums(nc):
         assert np.array_equal(out.cpu().numpy(), ref), (nc, v)
 
 
+@pytest.mark.parametrize("nc", [1, 2, 3, 4, 5, 7, 8, 9, 17, 33])
+def test_u8_row_groups(nc):
+    """The matrix-core sums take input rows four at a time: every remainder
+    of rows, DM trials and samples one either side of the tile edges, bytes at
+    both ends of their range."""
+    dd = _dd()
+    rng = np.random.default_rng(100 + nc)
+    f = 134.875 + (np.arange(nc) + 0.5) * 6.25 / nc
+    names = dd.variant_names("u8")
+    for nd, ns in [(15, 511), (17, 513), (31, 1023), (33, 1025), (65, 2049)]:
+        dms = np.arange(nd) * 0.01
+        delta = oracle.delay_table(f, 5e-6, dms)
+        nin = ns + int(delta.max())
+        x = rng.choice(np.array([0, 1, 127, 128, 254, 255], np.uint8), size=(2, nc, nin))
+        ref = oracle.forward_u8(x, delta, ns)
+        plan = dd.Plan(f, 5e-6, dms)
+        xg = _to_gpu(x, pad_extra=16)
+        for v in _variants(plan, "u8"):
+            if v < 0 or not names[v].startswith("u8m_"):
+                continue
+            _note(f"u8 row groups {(nc, nd, ns)} variant {names[v]}")
+            plan.set_variant(v, "u8")
+            out = dd.dedisperse(xg, plan, nsamp=ns)
+            torch.cuda.synchronize()
+            assert np.array_equal(out.cpu().numpy(), ref), (nc, nd, ns, names[v])
+
+
 def _sample_points(rng, nb, nd, ns, n):
     pb = rng.integers(0, nb, n)
     pd = rng.integers(0, nd, n)
