@@ -113,10 +113,12 @@ dedisp_status dedisp_plan_prepare(dedisp_plan plan, dedisp_dtype in_type, int32_
  *   d_in      [nbeam][nchan][in_stride] of in_type (F32 or U8)
  *   d_w       [nchan] float32 weights, or NULL for all ones (must be NULL for U8)
  *   d_out     [nbeam][ndm][out_stride] of out_type (F32 for F32 input, I32 for U8)
- * Beams share the plan's delays and weights.  Uses the plan's tuned kernel
- * variant for this dtype when one was chosen by dedisp_autotune, otherwise
- * the default; falls back to a direct (untiled) kernel when no tiled variant
- * fits the plan's delay spans.  Asynchronous on `stream`.
+ * Beams share the plan's delays and weights.  Uses the plan's kernel variant
+ * for this dtype when one was chosen by dedisp_autotune or
+ * dedisp_plan_set_variant, otherwise the default (dedisp_plan_variant) or one
+ * of a few finer-tiled variants prepared with it, whichever is estimated to be
+ * fastest for nbeam x nsamp; falls back to a direct (untiled) kernel when no
+ * tiled variant fits the plan's delay spans.  Asynchronous on `stream`.
  * Errors: DEDISP_E_INVALID (NULL plan or pointer, nbeam < 1, nsamp < 1),
  * DEDISP_E_DTYPE, DEDISP_E_SHAPE (in_stride < nsamp + max_delay,
  * out_stride < nsamp, rows longer than 2^29 samples, or more than 65535
@@ -355,7 +357,9 @@ const char* dedisp_variant_name(dedisp_dtype in_type, int32_t i);
  * (allocates).  DEDISP_E_UNTUNED if the variant does not fit the plan. */
 dedisp_status dedisp_plan_set_variant(dedisp_plan plan, dedisp_dtype in_type, int32_t variant);
 
-/* Variant execute will use for in_type (-1 = direct kernel). */
+/* Variant chosen for in_type (-1 = direct kernel): the one set or tuned, else
+ * the default, which calls too small to fill the GPU with it replace by a
+ * finer-tiled one. */
 int32_t dedisp_plan_variant(dedisp_plan plan, dedisp_dtype in_type);
 
 /* The same for the adjoint (float32 variants; -1 = direct adjoint kernel). */

@@ -35,7 +35,7 @@ DEVICE_FLAGS = [
     "-Wall", "-Wno-unused-function",
 ]
 
-SOURCES = ["engine.hip", "u8.hip", "detect.hip", "plan.cpp", "batch.cpp", "tune.cpp", "detect.cpp"]
+SOURCES = ["engine.hip", "engine_detect.hip", "engine_batch.hip", "u8.hip", "lane.hip", "tables.hip", "detect.hip", "plan.cpp", "batch.cpp", "tune.cpp", "detect.cpp"]
 
 
 def _gen():

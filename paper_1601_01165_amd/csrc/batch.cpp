@@ -104,6 +104,7 @@ static void drop_work(dedisp_batch b) {
 // b->nqueue queues.
 static dedisp_status build_work(dedisp_batch b, int vi) {
   const Variant& v = variants_f32()[vi];
+  if (v.kind != KIND_WIN_F32) return fail(DEDISP_E_UNTUNED, std::string(v.name) + ": no persistent form");
   std::vector<BeamDesc> beams(b->nbeam);
   std::vector<int64_t> cost(b->nbeam);
   int64_t total = 0;
@@ -225,6 +226,7 @@ static int tune_batch(dedisp_batch b, float* best_out) {
   // every variant once, then the three fastest again, more carefully
   std::vector<std::pair<float, int>> first;
   for (int vi = 0; vi < (int)vs.size(); ++vi) {
+    if (vs[vi].kind != KIND_WIN_F32) continue;
     const float ms = time_variant(vi, 1, 1);
     if (ms > 0) first.push_back({ms, vi});
   }
@@ -359,7 +361,7 @@ dedisp_status dedisp_batch_create(dedisp_batch* out, int32_t nbeam, const dedisp
   }
   if (vi < 0) {
     for (int k : default_order(0)) {
-      bool ok = true;
+      bool ok = variants_f32()[k].kind == KIND_WIN_F32;
       for (int i = 0; i < nbeam && ok; ++i) ok = ensure_tables(b->plans[i], 0, k, nullptr) == DEDISP_OK;
       if (ok) {
         vi = k;
@@ -434,6 +436,8 @@ dedisp_status dedisp_batch_set_variant(dedisp_batch b, int32_t variant) {
   if (!b) return fail(DEDISP_E_INVALID, "batch is NULL");
   if (variant < 0 || variant >= (int32_t)variants_f32().size())
     return fail(DEDISP_E_INVALID, "variant index out of range");
+  if (variants_f32()[variant].kind != KIND_WIN_F32)
+    return fail(DEDISP_E_UNTUNED, std::string(variants_f32()[variant].name) + ": no persistent form");
   for (int i = 0; i < b->nbeam; ++i) {
     dedisp_status st = ensure_tables(b->plans[i], 0, variant, nullptr);
     if (st != DEDISP_OK) return st;

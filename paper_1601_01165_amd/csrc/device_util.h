@@ -44,6 +44,15 @@ __device__ __forceinline__ T* uniform_ptr(T* p) {
   return reinterpret_cast<T*>(((uint64_t)hi << 32) | lo);
 }
 
+// A table the kernel only reads, in the constant address space: wave-uniform
+// elements become scalar loads that the compiler may issue early.
+template <typename T>
+using const_table = const T __attribute__((address_space(4))) *;
+template <typename T>
+__device__ __forceinline__ const_table<T> uniform_table(const T* p) {
+  return (const_table<T>)reinterpret_cast<uint64_t>(uniform_ptr(p));
+}
+
 // Wave-uniform scalar loads (wait included) of a table entry and a weight.
 typedef int32_t ent2_t __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ ent2_t sload_entry2(const int32_t* p) {

@@ -417,6 +417,8 @@ JMP_VARIANTS = [
     (20, 4, 40, 10, 8),
     (20, 4, 44, 8, 4),
     (20, 4, 44, 10, 4),
+    (20, 4, 84, 8, 4),
+    (20, 4, 84, 3, 4),
 ]
 
 

@@ -7,6 +7,7 @@
 
 #include <functional>
 #include <map>
+#include <memory>
 #include <string>
 #include <vector>
 
@@ -23,7 +24,7 @@ namespace dd {
 // staged in LDS per pass (cc) and the LDS row capacity (rowcap); the direct
 // kernel is the "no local memory, no reuse" end of the space.
 // ---------------------------------------------------------------------------
-enum Kind { KIND_WIN_F32 = 0, KIND_TILE_U8 = 1 };
+enum Kind { KIND_WIN_F32 = 0, KIND_TILE_U8 = 1, KIND_LANE_F32 = 2 };
 
 // Longest row (samples) accepted: row byte sizes must fit a 32-bit buffer
 // range, and sample indices an int, with room for tile overhang.
@@ -48,36 +49,37 @@ struct Variant {
   // f32 only: 1 = each row's DM slots branch into static blocks of adds; the table then holds block byte
   // offsets o * (4 * tp + 4) in place of the window offsets o
   int jmp = 0;
-  int st() const { return kind == KIND_WIN_F32 ? 64 * tp : 256 * tp; }
-  int dt() const { return nwave * dpw; }
+  __host__ __device__ int st() const { return kind == KIND_TILE_U8 ? 256 * tp : 64 * tp; }
+  __host__ __device__ int dt() const { return nwave * dpw; }
   // ints per wave-table entry: f32 {win_start, nl, one offset per row} padded to 4/8/16; u8 packed u16
   // offsets (mode 0) or one LDS byte offset per row (byte-shifted modes)
-  int wav_ints() const {
+  __host__ __device__ int wav_ints() const {
+    if (kind == KIND_LANE_F32) return dpw;  // one LDS byte offset per row
     if (kind == KIND_WIN_F32) return dpw + 2 <= 4 ? 4 : dpw + 2 <= 8 ? 8 : 16;
     return mode == 0 ? 4 : (dpw <= 4 ? 4 : 8);
   }
 };
 
 const std::vector<Variant>& variants_f32();
+void lane_variants(std::vector<Variant>& r);  // appends the lane kernels (lane.hip)
 const std::vector<Variant>& variants_u8();
 // Variant indices in order of preference when nothing was tuned (dir: 0 forward
 // FP32, 1 forward uint8, 2 adjoint); every index of the direction's list appears.
 const std::vector<int>& default_order(int dir);
 
-// Host-built tile tables for one variant on one delay matrix.
+// Tile tables for one variant on one delay matrix, built on the GPU (tables.hip).
 //   blk[row_tile][rows_in]            {stage_base, stage_len}
 //   wav[wave_tile][rows_in][wav_ints] f32: {win_start, nl, offset of each row...} (jump form: offset times
 //                                      the block size)
 //                                      u8:  {packed u16 offsets...} or {LDS byte offset of each row...}
+//                                      f32 lane kernels: {LDS byte offset of each row...}
 struct Tables {
   int variant = -1;
   int n_row_tiles = 0;
-  int n_wave_tiles = 0;
-  int max_stage = 0;
+  std::shared_ptr<void> mem;  // the device memory they lie in (several variants' may share it)
   int32_t* d_blk = nullptr;
   int32_t* d_wav = nullptr;
   int32_t* d_span = nullptr;  // adjoint: per (row tile, pass) {least stage base, greatest stage end}
-  size_t bytes = 0;
   int pins = 0;  // batches whose work table points at these tables (never freed while pinned)
 };
 
@@ -140,6 +142,17 @@ hipError_t launch_tiled(const Variant& v, const TileArgs& a, int nbeam, bool adj
 // uint8 variants (u8.hip); grid: tile blocks x beams.
 hipError_t launch_tiled_u8(const Variant& v, const TileArgs& a, dim3 grid, hipStream_t s);
 hipError_t launch_detect_u8(const Variant& v, const TileArgs& a, dim3 grid, hipStream_t s);
+// Lane kernels (lane.hip).
+hipError_t launch_lane(const Variant& v, const TileArgs& a, dim3 grid, bool adjoint, hipStream_t s);
+// Build a variant's tables from the delay matrix [ndm][nchan] (span: adjoint, or
+// null); the variant must fit.
+hipError_t launch_build_tables(const Variant& v, const int32_t* d_delay, int nchan, int ndm, bool adjoint, int pad,
+                               int32_t* blk, int32_t* wav, int32_t* span, hipStream_t s);
+// Whether up to kFitBatch variants fit the delay matrix: bad[k] = 0 or why not.
+constexpr int kFitBatch = 16;
+enum { kTablesWindow = 1, kTablesRow = 2, kTablesOffset = 3, kTablesPacked = 4 };
+hipError_t launch_check_fits(const std::vector<const Variant*>& vs, const int32_t* d_delay, int nchan, int ndm,
+                             bool adjoint, int pad, int* bad, hipStream_t s);
 hipError_t launch_direct_f32(const float* in, int64_t in_stride, int64_t in_beam_stride, const int32_t* delta,
                              int nchan, int ndm, const float* w, float* out, int64_t out_stride,
                              int64_t out_beam_stride, int nsamp, int nbeam, hipStream_t s);
@@ -214,9 +227,15 @@ struct dedisp_plan_s {
   std::vector<double> freq, dm;
   std::vector<int32_t> delay;       // [ndm][nchan]
   int32_t* d_delay = nullptr;       // device copy [ndm][nchan]
+  int* d_bad = nullptr;             // kFitBatch results of the fit check (after the delays)
+  std::map<int, int> fits[3];       // per direction and variant: 0 fits, else why not
   // adjoint view: out rows = channels, in rows = DMs, delay' = pad - delay
   int adj_pad = 0;                  // max_delay rounded up to a multiple of 4
   std::map<int, dd::Tables> fwd_f32, fwd_u8, adj_f32;
   int var_f32 = -2, var_u8 = -2, var_adj = -2;  // -1 = direct kernel, -2 = not chosen yet
+  // per direction (0 forward FP32, 1 forward uint8, 2 adjoint): each call picks
+  // between the default variant and these by its size (until one is set or tuned)
+  bool by_size[3] = {false, false, false};
+  std::vector<int> fine[3];
   int var_det_f32 = -2, var_det_u8 = -2;         // single-pulse search: -1 = unfused, -2 = automatic
 };

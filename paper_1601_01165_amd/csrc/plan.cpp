@@ -5,12 +5,10 @@
 
 #include <algorithm>
 #include <climits>
-#include <atomic>
 #include <cstdio>
 #include <functional>
 #include <map>
 #include <mutex>
-#include <thread>
 #include <limits>
 #include <new>
 #include <string>
@@ -61,154 +59,80 @@ static dedisp_status build_delay_table(int nchan, const double* f, double tsamp,
   return DEDISP_OK;
 }
 
-// ---------------------------------------------------------------------------
-// Tile tables.  `delay(r, c)` is the delay of output row r for input row c.
-// Output rows are grouped in block tiles of v.dt() rows and wave tiles of
-// v.dpw rows; rows past the end repeat the last row (their results are not
-// stored).
-// ---------------------------------------------------------------------------
-// Runs f(i) for i in [0, n) on the host's cores (the tables of large plans
-// and batches are built per block row tile, independently).
-template <class F>
-static void parallel_for(int n, F&& f) {
-  const int nt = std::min<int>(n, std::max(1u, std::min(16u, std::thread::hardware_concurrency())));
-  if (nt <= 1 || n < 4) {
-    for (int i = 0; i < n; ++i) f(i);
-    return;
-  }
-  std::atomic<int> next(0);
-  std::vector<std::thread> th;
-  th.reserve(nt);
-  for (int t = 0; t < nt; ++t)
-    th.emplace_back([&]() {
-      for (int i; (i = next.fetch_add(1)) < n;) f(i);
-    });
-  for (auto& x : th) x.join();
+// Device memory that is freed with its last user.
+static hipError_t shared_malloc(std::shared_ptr<void>& mem, size_t bytes) {
+  void* ptr = nullptr;
+  const hipError_t e = hipMalloc(&ptr, bytes);
+  if (e == hipSuccess) mem = std::shared_ptr<void>(ptr, [](void* q) { (void)hipFree(q); });
+  return e;
 }
 
-template <class DelayFn>
-static bool build_tables(const Variant& v, int rows_out, int rows_in, const DelayFn& delay, std::vector<int32_t>& blk,
-                         std::vector<int32_t>& wav, int& n_row_tiles, int& max_stage, std::string& why) {
-  const int DT = v.dt(), DPW = v.dpw, NW = v.nwave, WI = v.wav_ints();
-  if (v.kind == KIND_TILE_U8 && v.mode == 1 && rows_in > 256) {
-    why = "more than 256 input rows overflow its packed sums";
-    return false;
-  }
-  n_row_tiles = (rows_out + DT - 1) / DT;
-  const int n_wave_tiles = n_row_tiles * NW;
-  blk.assign((size_t)n_row_tiles * rows_in * 2, 0);
-  // room for a whole pass's entries after the last row (read, not used)
-  wav.assign(((size_t)n_wave_tiles * rows_in + v.cc) * WI, 0);
-  std::vector<int> stage_max(n_row_tiles, 0);
-  std::atomic<int> bad(0);  // 1: window span, 2: LDS row, 3: 16-bit offset
-  parallel_for(n_row_tiles, [&](int rt) {
-    std::vector<int> d(DT);
-    int smax = 0;
-    for (int c = 0; c < rows_in && !bad.load(std::memory_order_relaxed); ++c) {
-      for (int k = 0; k < DT; ++k) d[k] = delay(std::min(rt * DT + k, rows_out - 1), c);
-      if (v.kind == KIND_WIN_F32) {
-        const int bmin = *std::min_element(d.begin(), d.end());
-        const int sbase = bmin & ~3;
-        int need = 0;
-        for (int w = 0; w < NW; ++w) {
-          const int* dw = &d[w * DPW];
-          const int wmin = *std::min_element(dw, dw + DPW);
-          const int ws = (wmin - sbase) & ~3;
-          int maxo = 0;
-          int32_t* e = &wav[(((size_t)(rt * NW + w)) * rows_in + c) * WI];
-          for (int j = 0; j < DPW; ++j) {
-            const int o = dw[j] - sbase - ws;
-            if (o < 0 || o > v.nwin - v.tp) {
-              bad.store(1);
-              return;
-            }
-            maxo = std::max(maxo, o);
-            e[2 + j] = v.jmp ? o * (4 * v.tp + 4) : o;
-          }
-          const int nl = std::max(v.tp / 4 + 1, (v.tp + maxo + 3) / 4);
-          e[0] = ws;
-          e[1] = nl;
-          // full-window variants read all nwin samples of every row
-          need = std::max(need, ws + 63 * v.tp + (v.jmp == 2 ? v.nwin : 4 * nl));
-        }
-        need = (need + 3) & ~3;
-        if (need > v.rowcap) {
-          bad.store(2);
-          return;
-        }
-        blk[((size_t)rt * rows_in + c) * 2 + 0] = sbase;
-        blk[((size_t)rt * rows_in + c) * 2 + 1] = need;
-        smax = std::max(smax, need);
-      } else {
-        const int bmin = *std::min_element(d.begin(), d.end());
-        const int sbase = bmin & ~15;
-        int need = 0;
-        for (int w = 0; w < NW; ++w) {
-          const int* dw = &d[w * DPW];
-          int32_t* e = &wav[(((size_t)(rt * NW + w)) * rows_in + c) * WI];
-          for (int j = 0; j < DPW; ++j) {
-            const int o = dw[j] - sbase;
-            if (o < 0 || o > 65535) {
-              bad.store(3);
-              return;
-            }
-            if (v.mode == 0) {
-              e[j / 2] |= (int32_t)((uint32_t)o << (16 * (j % 2)));
-            } else {  // modes 1 to 3
-              // byte offset into the staged copies: copy o & 3, row slot c % cc, dword o >> 2
-              e[j] = 4 * (((o & 3) * v.cc + c % v.cc) * (v.rowcap / 4) + (o >> 2));
-            }
-            need = std::max(need, (o & ~3) + 256 * v.tp + 4);
-          }
-        }
-        need = (need + 15) & ~15;
-        if (need > v.rowcap) {
-          bad.store(2);
-          return;
-        }
-        blk[((size_t)rt * rows_in + c) * 2 + 0] = sbase;
-        blk[((size_t)rt * rows_in + c) * 2 + 1] = need;
-        smax = std::max(smax, need);
-      }
-    }
-    stage_max[rt] = smax;
-  });
-  switch (bad.load()) {
-    case 1: why = "delay span within a wave exceeds the register window"; return false;
-    case 2: why = "delay span within a block exceeds the LDS row"; return false;
-    case 3: why = "delay span exceeds the 16-bit offset range"; return false;
-    default: break;
-  }
-  max_stage = 0;
-  for (int m : stage_max) max_stage = std::max(max_stage, m);
-  return true;
-}
-
-static void free_tables(Tables& t) {
-  if (t.d_blk) (void)hipFree(t.d_blk);
-  if (t.d_wav) (void)hipFree(t.d_wav);
-  if (t.d_span) (void)hipFree(t.d_span);
-  t = Tables();
+// Sizes (ints, each part a multiple of 256 bytes) of a variant's tables.
+struct TableSizes {
+  size_t blk, ent, slack, span;
+  size_t total() const { return blk + ent + slack + span; }
+};
+static TableSizes table_sizes(dedisp_plan p, int dir, const Variant& v) {
+  const bool adj = dir == 2;
+  const size_t rows_out = adj ? p->nchan : p->ndm, rows_in = adj ? p->ndm : p->nchan;
+  const size_t nrt = (rows_out + v.dt() - 1) / v.dt();
+  auto whole = [](size_t n) { return (n + 63) / 64 * 64; };
+  TableSizes s;
+  s.blk = whole(nrt * rows_in * 2);
+  s.ent = nrt * v.nwave * rows_in * v.wav_ints();
+  s.slack = whole(s.ent + (size_t)v.cc * v.wav_ints()) - s.ent;  // a whole pass can be read after the last row
+  // The adjoint's input rows (DM trials) reach outside the output gradient's
+  // samples for part of the time tiles: the span of each pass's staged
+  // windows lets the kernel skip passes that would add only zeros.
+  s.span = adj ? whole(nrt * ((rows_in + v.cc - 1) / v.cc) * 2) : 0;
+  return s;
 }
 
 void drop_spare_tables(dedisp_plan p, int dir, int keep) {
   std::map<int, Tables>& m = dir == 0 ? p->fwd_f32 : dir == 1 ? p->fwd_u8 : p->adj_f32;
   for (auto it = m.begin(); it != m.end();) {
     const int vi = it->first;
-    const bool chosen = vi == keep || (dir == 0 && (vi == p->var_f32 || vi == p->var_det_f32)) ||
+    const std::vector<int>& fine = p->fine[dir];
+    const bool chosen = vi == keep || (p->by_size[dir] && std::find(fine.begin(), fine.end(), vi) != fine.end()) || (dir == 0 && (vi == p->var_f32 || vi == p->var_det_f32)) ||
                         (dir == 1 && (vi == p->var_u8 || vi == p->var_det_u8)) || (dir == 2 && vi == p->var_adj);
     if (chosen || it->second.pins > 0) {
       ++it;
       continue;
     }
-    free_tables(it->second);
     it = m.erase(it);
   }
 }
 
-// Build and upload the tables of variant `vi` in direction `dir`
-// (0 = forward f32, 1 = forward u8, 2 = adjoint f32).
-dedisp_status ensure_tables(dedisp_plan p, int dir, int vi, Tables** out) {
+// Learn which of the variants fit the plan in direction `dir` (0 = forward f32,
+// 1 = forward u8, 2 = adjoint f32), as many as possible in one launch.
+static dedisp_status check_fits(dedisp_plan p, int dir, const std::vector<int>& ids) {
+  const std::vector<Variant>& vs = dir == 1 ? variants_u8() : variants_f32();
+  const int rows_in = dir == 2 ? p->ndm : p->nchan;
+  std::vector<int> ask;
+  for (int vi : ids) {
+    if (p->fits[dir].count(vi)) continue;
+    if (vs[vi].kind == KIND_TILE_U8 && vs[vi].mode == 1 && rows_in > 256)
+      p->fits[dir][vi] = kTablesPacked;
+    else
+      ask.push_back(vi);
+  }
+  for (size_t k0 = 0; k0 < ask.size(); k0 += kFitBatch) {
+    const size_t n = std::min<size_t>(kFitBatch, ask.size() - k0);
+    std::vector<const Variant*> list;
+    for (size_t k = 0; k < n; ++k) list.push_back(&vs[ask[k0 + k]]);
+    int bad[kFitBatch];
+    hipError_t e = launch_check_fits(list, p->d_delay, p->nchan, p->ndm, dir == 2, p->adj_pad, p->d_bad, nullptr);
+    if (e == hipSuccess) e = hipMemcpy(bad, p->d_bad, n * sizeof(int), hipMemcpyDeviceToHost);
+    if (e != hipSuccess) return hip_fail(e, "checking which kernels fit");
+    for (size_t k = 0; k < n; ++k) p->fits[dir][ask[k0 + k]] = bad[k];
+  }
+  return DEDISP_OK;
+}
+
+// Build the tables of variant `vi` in direction `dir`, in memory of their own or
+// from int `at` of `mem`; the build may still be running on the null stream on
+// return.
+static dedisp_status build_tables(dedisp_plan p, int dir, int vi, Tables** out, std::shared_ptr<void> mem, size_t at) {
   std::map<int, Tables>& m = dir == 0 ? p->fwd_f32 : dir == 1 ? p->fwd_u8 : p->adj_f32;
   auto it = m.find(vi);
   if (it != m.end()) {
@@ -217,84 +141,120 @@ dedisp_status ensure_tables(dedisp_plan p, int dir, int vi, Tables** out) {
   }
   const std::vector<Variant>& vs = dir == 1 ? variants_u8() : variants_f32();
   if (vi < 0 || vi >= (int)vs.size()) return fail(DEDISP_E_INVALID, "variant index out of range");
+  const dedisp_status st = check_fits(p, dir, {vi});
+  if (st != DEDISP_OK) return st;
   const Variant& v = vs[vi];
-  std::vector<int32_t> blk, wav;
-  int nrt = 0, maxs = 0;
-  std::string why;
-  bool ok;
-  const int C = p->nchan, D = p->ndm;
-  const int32_t* del = p->delay.data();
-  if (dir == 2) {
-    const int pad = p->adj_pad;
-    ok = build_tables(v, C, D, [&](int r, int c) { return pad - del[(size_t)c * C + r]; }, blk, wav, nrt, maxs, why);
-  } else {
-    ok = build_tables(v, D, C, [&](int r, int c) { return del[(size_t)r * C + c]; }, blk, wav, nrt, maxs, why);
-  }
-  if (!ok) return fail(DEDISP_E_UNTUNED, std::string(v.name) + ": " + why);
-  // The adjoint's input rows (DM trials) reach outside the output gradient's
-  // samples for part of the time tiles: the span of each pass's staged
-  // windows lets the kernel skip passes that would add only zeros.
-  std::vector<int32_t> span;
-  if (dir == 2) {
-    const int rows_in = D, npass = (rows_in + v.cc - 1) / v.cc;
-    span.assign((size_t)nrt * npass * 2, 0);
-    for (int rt = 0; rt < nrt; ++rt)
-      for (int q = 0; q < npass; ++q) {
-        int smin = INT32_MAX, emax = INT32_MIN;
-        for (int c = q * v.cc; c < std::min(rows_in, (q + 1) * v.cc); ++c) {
-          const int32_t* b = &blk[((size_t)rt * rows_in + c) * 2];
-          smin = std::min(smin, b[0]);
-          emax = std::max(emax, b[0] + b[1]);
-        }
-        span[((size_t)rt * npass + q) * 2 + 0] = smin;
-        span[((size_t)rt * npass + q) * 2 + 1] = emax;
-      }
-  }
+  static const char* const why[] = {"", "delay span within a wave exceeds the register window",
+                                    "delay span within a block exceeds the LDS row",
+                                    "delay span exceeds the 16-bit offset range",
+                                    "more than 256 input rows overflow its packed sums"};
+  if (p->fits[dir][vi]) return fail(DEDISP_E_UNTUNED, std::string(v.name) + ": " + why[p->fits[dir][vi]]);
+  const TableSizes n = table_sizes(p, dir, v);
+  hipError_t e = mem ? hipSuccess : shared_malloc(mem, n.total() * sizeof(int32_t));
   Tables t;
-  t.variant = vi;
-  t.n_row_tiles = nrt;
-  t.n_wave_tiles = nrt * v.nwave;
-  t.max_stage = maxs;
-  t.bytes = (blk.size() + wav.size() + span.size()) * sizeof(int32_t);
-  hipError_t e = hipMalloc(&t.d_blk, blk.size() * sizeof(int32_t));
-  if (e == hipSuccess) e = hipMalloc(&t.d_wav, wav.size() * sizeof(int32_t));
-  if (e == hipSuccess && !span.empty()) e = hipMalloc(&t.d_span, span.size() * sizeof(int32_t));
-  if (e == hipSuccess) e = hipMemcpy(t.d_blk, blk.data(), blk.size() * sizeof(int32_t), hipMemcpyHostToDevice);
-  if (e == hipSuccess) e = hipMemcpy(t.d_wav, wav.data(), wav.size() * sizeof(int32_t), hipMemcpyHostToDevice);
-  if (e == hipSuccess && !span.empty())
-    e = hipMemcpy(t.d_span, span.data(), span.size() * sizeof(int32_t), hipMemcpyHostToDevice);
-  if (e != hipSuccess) {
-    free_tables(t);
-    return e == hipErrorOutOfMemory ? fail(DEDISP_E_NOMEM, "device allocation of tile tables failed")
-                                    : hip_fail(e, "uploading tile tables");
+  if (e == hipSuccess) {
+    t.variant = vi;
+    t.n_row_tiles = ((dir == 2 ? p->nchan : p->ndm) + v.dt() - 1) / v.dt();
+    t.mem = mem;
+    t.d_blk = static_cast<int32_t*>(mem.get()) + at;
+    t.d_wav = t.d_blk + n.blk;
+    if (n.span) t.d_span = t.d_wav + n.ent + n.slack;
+    e = hipMemsetAsync(t.d_wav + n.ent, 0, n.slack * sizeof(int32_t), nullptr);
   }
+  if (e == hipSuccess)
+    e = launch_build_tables(v, p->d_delay, p->nchan, p->ndm, dir == 2, p->adj_pad, t.d_blk, t.d_wav, t.d_span, nullptr);
+  if (e != hipSuccess)
+    return e == hipErrorOutOfMemory ? fail(DEDISP_E_NOMEM, "device allocation of tile tables failed")
+                                    : hip_fail(e, "building tile tables");
   auto res = m.emplace(vi, t);
   if (out) *out = &res.first->second;
   return DEDISP_OK;
+}
+
+dedisp_status ensure_tables(dedisp_plan p, int dir, int vi, Tables** out) {
+  std::map<int, Tables>& m = dir == 0 ? p->fwd_f32 : dir == 1 ? p->fwd_u8 : p->adj_f32;
+  const bool have = m.count(vi) != 0;
+  const dedisp_status st = build_tables(p, dir, vi, out, nullptr, 0);
+  if (st != DEDISP_OK || have) return st;
+  const hipError_t e = hipStreamSynchronize(nullptr);  // complete for every stream
+  return e == hipSuccess ? DEDISP_OK : hip_fail(e, "building tile tables");
 }
 
 // Variant preference when nothing was tuned, fastest first as measured on
 // MI355X: forward FP32 on the 1024-channel, 2048-DM beam; forward uint8 on the
 // 32-channel, 2048-DM beam (the packed sums of variant 22 take at most 256
 // channels; past that the matrix-core shapes are 1.3 times as fast as the flushed
-// packed sums, 1.06 against 1.41 ms on 1024 channels); the adjoint on 32 beams of 1024 channels and
-// 1024 DMs.  Variants with wide register windows or int32 sums come last:
-// they fit the widest delay spans and the most channels.
+// packed sums, 1.06 against 1.41 ms on 1024 channels); the adjoint on 32 beams of
+// 1024 channels and 1024 DMs.  The widest register windows and int32 sums come
+// late: they fit the widest delay spans and the most channels.  In the adjoint
+// the window of 84 comes right after those of 44: neighbouring channels differ by
+// up to 12 samples on 1024 channels and 2048 DM trials, which only the
+// 8-sample-per-lane forms took before (2.08 against 5.62 ms).
 const std::vector<int>& default_order(int dir) {
-  static const std::vector<int> f32 = {35, 34, 37, 38, 36, 32, 33, 22, 28, 21, 29, 31, 23, 30, 19, 20, 25, 24, 27, 26, 15, 18, 13,
-                                       17, 9,  8,  16, 6,  14, 11, 7,  12, 10, 2,  3,  0,  1,  5,  4};
+  static const std::vector<int> f32 = {35, 34, 37, 38, 36, 32, 33, 22, 28, 21, 29, 31, 23, 30, 19, 20, 39, 40, 25, 24, 27, 26, 15, 18, 13,
+                                       17, 9,  8,  16, 6,  14, 11, 7,  12, 10, 2,  3,  0,  1,  5,  4,  43, 45, 42, 44, 41};
   static const std::vector<int> u8 = {22, 23, 25, 27, 26, 24, 16, 20, 15, 21, 12, 13, 17, 14, 18, 6, 2, 0, 5, 19, 9, 3, 4, 1, 8, 7, 10, 11};
-  static const std::vector<int> adj = {37, 38, 26, 27, 32, 34, 35, 36, 33, 19, 21, 29, 20, 30, 9, 8, 6, 11, 12, 7, 10, 13, 22, 28,
-                                       18, 15, 23, 31, 17, 16, 25, 24, 14, 2, 3, 1, 0, 5, 4};
+  static const std::vector<int> adj = {37, 38, 39, 40, 26, 27, 32, 34, 35, 36, 33, 19, 21, 29, 20, 30, 9, 8, 6, 11, 12, 7, 10, 13, 22, 28,
+                                       18, 15, 23, 31, 17, 16, 25, 24, 14, 2, 3, 1, 0, 5, 4, 43, 44, 42, 45, 41};
   return dir == 1 ? u8 : dir == 2 ? adj : f32;
 }
 
-// Default variant choice: the first of the preference order whose tables
-// build (else -1, the direct kernel).
-static int default_variant(dedisp_plan p, int dir) {
-  for (int vi : default_order(dir))
-    if (ensure_tables(p, dir, vi, nullptr) == DEDISP_OK) return vi;
-  return -1;
+// The choice by size.  A plan that was not tuned keeps, beside its default
+// variant, a few with smaller tiles, and each call takes the one with the least
+// estimated time per input row,
+//   max(alone, rounds * full),   rounds = ceil(blocks / CUs),
+// in microseconds measured on MI355X: `alone` with at most one block per CU (the
+// latency of a row's step), `full` a block's share of a CU that holds as many as
+// fit.  The coarse tiles have the best throughput (64 DM trials x 1280 samples:
+// 39 adds per ns over the chip; 16 x 256 in LDS: 17), the fine ones occupy the chip
+// with little work: 1024 channels, 301 DM trials, 2003 samples are 10 coarse
+// tiles in 473 us or 304 fine ones in 103 us, while 370 channels, 1072 DM trials,
+// 11,790 samples are 170 coarse tiles in 193 us and 315 us in fine ones.  On the
+// shapes swept the estimate is within 15 % of the time.
+struct SizeCost {
+  int vi;
+  float alone, full;
+};
+static const std::vector<SizeCost>& size_costs(int dir) {
+  static const std::vector<SizeCost> f32 = {{35, .47f, .508f}, {41, .100f, .036f}, {42, .132f, .061f}};
+  static const std::vector<SizeCost> u8 = {{22, .50f, .51f},  {23, .27f, .207f},
+                                           {25, .18f, .125f}, {26, .13f, .079f}, {27, .14f, .150f}};
+  static const std::vector<SizeCost> adj = {{37, .47f, .508f}, {39, .50f, .500f}, {41, .100f, .036f}, {43, .178f, .125f}};
+  return dir == 1 ? u8 : dir == 2 ? adj : f32;
+}
+
+static float size_cost(dedisp_plan p, int dir, const Variant& v, int nbeam, int64_t nout) {
+  // variants without a measured pair (wide spans): the coarse tile's rate, scaled by the tile
+  SizeCost c = {v.id, .47f, .508f * (float)(v.dt() * v.st()) / (64 * 1280)};
+  for (const SizeCost& k : size_costs(dir))
+    if (k.vi == v.id) c = k;
+  const int64_t rows_out = dir == 2 ? p->nchan : p->ndm;
+  const int64_t blocks = (rows_out + v.dt() - 1) / v.dt() * ((nout + v.st() - 1) / v.st()) * nbeam;
+  return std::max(c.alone, (float)((blocks + p->ncu - 1) / p->ncu) * c.full);
+}
+
+// The variant a call of nbeam x nout output samples runs (-1: direct).
+static int pick_variant(dedisp_plan p, int dir, int nbeam, int64_t nout) {
+  const int main = dir == 0 ? p->var_f32 : dir == 1 ? p->var_u8 : p->var_adj;
+  if (!p->by_size[dir] || main < 0) return main;
+  const std::vector<Variant>& vs = dir == 1 ? variants_u8() : variants_f32();
+  // from 16 blocks per CU on the int32 stores bind, and the packed sums of the
+  // default uint8 shape are as fast as any (0.40 ms against 0.41 to 0.44 ms on 32
+  // channels, 2048 DM trials, 200,000 samples)
+  const Variant& mv = vs[main];
+  if (dir == 1 && mv.mode == 1 &&
+      (int64_t)((p->ndm + mv.dt() - 1) / mv.dt()) * ((nout + mv.st() - 1) / mv.st()) * nbeam >= 16 * (int64_t)p->ncu)
+    return main;
+  int best = main;
+  float least = size_cost(p, dir, mv, nbeam, nout);
+  for (int vi : p->fine[dir]) {
+    const float c = size_cost(p, dir, vs[vi], nbeam, nout);
+    if (c < least) {
+      least = c;
+      best = vi;
+    }
+  }
+  return best;
 }
 
 static bool aligned16(const void* ptr) { return ((uintptr_t)ptr & 15u) == 0; }
@@ -303,7 +263,39 @@ static bool aligned16(const void* ptr) { return ((uintptr_t)ptr & 15u) == 0; }
 // use or by dedisp_plan_prepare; -2 marks "not chosen yet".
 static void ensure_chosen(dedisp_plan p, int dir) {
   int& v = dir == 0 ? p->var_f32 : dir == 1 ? p->var_u8 : p->var_adj;
-  if (v == -2) v = default_variant(p, dir);
+  if (v != -2) return;
+  // the first of the preference order that fits (else the direct kernel), and
+  // what the choice by size may take beside it
+  const std::vector<int>& order = default_order(dir);
+  std::vector<int> ask(order.begin(), order.begin() + std::min<size_t>(4, order.size()));
+  for (const SizeCost& c : size_costs(dir)) ask.push_back(c.vi);
+  (void)check_fits(p, dir, ask);
+  auto fits = [&](int vi) { return check_fits(p, dir, {vi}) == DEDISP_OK && p->fits[dir][vi] == 0; };
+  const std::vector<Variant>& vs = dir == 1 ? variants_u8() : variants_f32();
+  int first = -1;
+  for (int vi : order)
+    if (fits(vi)) {
+      first = vi;
+      break;
+    }
+  std::vector<int> build;
+  if (first >= 0) build.push_back(first);
+  for (const SizeCost& c : size_costs(dir))
+    if (first >= 0 && c.vi != first && fits(c.vi)) build.push_back(c.vi);
+  size_t total = 0, at = 0;
+  for (int vi : build) total += table_sizes(p, dir, vs[vi]).total();
+  std::shared_ptr<void> mem;  // one allocation for all of them
+  if (total && shared_malloc(mem, total * sizeof(int32_t)) != hipSuccess) build.resize(1);
+  p->by_size[dir] = true;
+  p->fine[dir].clear();
+  for (int vi : build) {
+    const dedisp_status st = build_tables(p, dir, vi, nullptr, mem, at);
+    if (mem) at += table_sizes(p, dir, vs[vi]).total();
+    if (st != DEDISP_OK && vi == first) first = -1;
+    if (st == DEDISP_OK && vi != first) p->fine[dir].push_back(vi);
+  }
+  (void)hipStreamSynchronize(nullptr);  // the tables are complete for every stream
+  v = first;
 }
 
 // Scratch of the allocation-free adjoint (dedisp_adjoint_noalloc): the
@@ -347,7 +339,7 @@ static dedisp_status adjoint_impl(dedisp_plan p, int32_t nbeam, int32_t nsamp, i
   } else if (p->var_adj == -2) {
     return fail(DEDISP_E_INVALID, "the adjoint kernel is not chosen yet: call dedisp_plan_prepare first");
   }
-  const int vi = p->var_adj;
+  const int vi = pick_variant(p, 2, nbeam, nin);
   if (vi < 0) {
     e = launch_direct_adjoint(d_g, g_stride, g_stride * p->ndm, p->d_delay, p->nchan, p->ndm, nsamp, nin, d_w,
                               d_grad_in, gi_stride, gi_stride * p->nchan, d_in, in_stride, in_stride * p->nchan,
@@ -468,7 +460,7 @@ dedisp_status dedisp_plan_create(dedisp_plan* plan, int32_t nchan, const double*
   hipError_t e = hipGetDevice(&p->device);
   if (e == hipSuccess) e = hipDeviceGetAttribute(&p->ncu, hipDeviceAttributeMultiprocessorCount, p->device);
   if (e == hipSuccess && p->ncu < 1) p->ncu = 1;
-  if (e == hipSuccess) e = hipMalloc(&p->d_delay, p->delay.size() * sizeof(int32_t));
+  if (e == hipSuccess) e = hipMalloc(&p->d_delay, (p->delay.size() + kFitBatch) * sizeof(int32_t));
   if (e == hipSuccess)
     e = hipMemcpy(p->d_delay, p->delay.data(), p->delay.size() * sizeof(int32_t), hipMemcpyHostToDevice);
   if (e != hipSuccess) {
@@ -476,13 +468,14 @@ dedisp_status dedisp_plan_create(dedisp_plan* plan, int32_t nchan, const double*
     dedisp_plan_destroy(p);
     return st;
   }
+  p->d_bad = p->d_delay + p->delay.size();
   // the allocation-free adjoint's scratch on this device, looked up once
   if (!scratch_address(p->device)) {
     st = DEDISP_E_HIP;
     dedisp_plan_destroy(p);
     return st;
   }
-  p->var_f32 = default_variant(p, 0);
+  ensure_chosen(p, 0);
   *plan = p;
   return DEDISP_OK;
 }
@@ -503,8 +496,6 @@ dedisp_status dedisp_compute_delays(int32_t nchan, const double* freq_mhz, doubl
 
 dedisp_status dedisp_plan_destroy(dedisp_plan p) {
   if (!p) return DEDISP_OK;
-  for (auto* m : {&p->fwd_f32, &p->fwd_u8, &p->adj_f32})
-    for (auto& kv : *m) free_tables(kv.second);
   if (p->d_delay) (void)hipFree(p->d_delay);
   delete p;
   return DEDISP_OK;
@@ -545,6 +536,7 @@ dedisp_status dedisp_plan_set_variant(dedisp_plan p, dedisp_dtype t, int32_t vi)
     return fail(DEDISP_E_INVALID, "variant must be >= -1");
   }
   (t == DEDISP_U8 ? p->var_u8 : p->var_f32) = vi;
+  p->by_size[dir] = false;
   return DEDISP_OK;
 }
 
@@ -563,6 +555,7 @@ dedisp_status dedisp_plan_set_adjoint_variant(dedisp_plan p, int32_t vi) {
     return fail(DEDISP_E_INVALID, "variant must be >= -1");
   }
   p->var_adj = vi;
+  p->by_size[2] = false;
   return DEDISP_OK;
 }
 
@@ -603,7 +596,7 @@ dedisp_status dedisp_execute(dedisp_plan p, int32_t nbeam, int32_t nsamp, const 
     return fail(DEDISP_E_ALIGN, "pointers and row byte sizes must be multiples of 16 bytes");
   hipStream_t s = (hipStream_t)stream;
   ensure_chosen(p, u8 ? 1 : 0);
-  const int vi = u8 ? p->var_u8 : p->var_f32;
+  const int vi = pick_variant(p, u8 ? 1 : 0, nbeam, nsamp);
   hipError_t e;
   if (vi < 0) {
     if (u8)
@@ -670,7 +663,7 @@ dedisp_status dedisp_adjoint(dedisp_plan p, int32_t nbeam, int32_t nsamp, int32_
 
 size_t dedisp_adjoint_noalloc_bytes(dedisp_plan p, int32_t nbeam, int32_t nin) {
   if (!p || nbeam < 1 || nin < 1 || p->var_adj == -2) return 0;
-  const int vi = p->var_adj;
+  const int vi = pick_variant(p, 2, nbeam, nin);
   // one FP64 partial sum per channel and (beam, time part): 256-sample parts
   // for the direct kernel, the variant's time tiles otherwise
   const int64_t part = vi < 0 ? 256 : variants_f32()[vi].st();

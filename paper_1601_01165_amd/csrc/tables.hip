@@ -1,0 +1,171 @@
+// Tile tables built on the GPU from the plan's delay matrix (what they hold is
+// described with struct Tables): one thread per (block row tile, input row).
+#include <algorithm>
+
+#include "internal.h"
+
+namespace dd {
+
+namespace {
+
+// Delay of output row r for input row c: the plan's matrix, or its transpose
+// counted down from `pad` (adjoint).
+struct DelayView {
+  const int32_t* delta;
+  int nchan;
+  bool adj;
+  int pad;
+  __device__ int operator()(int r, int c) const {
+    return adj ? pad - delta[(size_t)c * nchan + r] : delta[(size_t)r * nchan + c];
+  }
+};
+
+// The tables' entries of input row c for row tile rt (not written when blk is
+// null); returns why they do not fit the variant, or 0.
+__device__ int table_column(const Variant& v, const DelayView& delay, int rows_out, int rows_in, int rt, int c,
+                            int32_t* blk, int32_t* wav) {
+  const int DT = v.nwave * v.dpw, WI = v.wav_ints();
+  // rows past the end repeat the last row (their results are not stored)
+  auto d = [&](int k) { return delay(min(rt * DT + k, rows_out - 1), c); };
+  int dmin = d(0);
+  for (int k = 1; k < DT; ++k) dmin = min(dmin, d(k));
+  const int sbase = v.kind == KIND_TILE_U8 ? dmin & ~15 : dmin & ~3;
+  int need = 0;
+  for (int w = 0; w < v.nwave; ++w) {
+    int32_t* e = blk ? wav + (((size_t)rt * v.nwave + w) * rows_in + c) * WI : nullptr;
+    if (v.kind == KIND_WIN_F32) {
+      int wmin = d(w * v.dpw);
+      for (int j = 1; j < v.dpw; ++j) wmin = min(wmin, d(w * v.dpw + j));
+      const int ws = (wmin - sbase) & ~3;
+      if (ws > v.rowcap) return kTablesRow;
+      int maxo = 0;
+      for (int j = 0; j < v.dpw; ++j) {
+        const int o = d(w * v.dpw + j) - sbase - ws;
+        if (o < 0 || o > v.nwin - v.tp) return kTablesWindow;
+        maxo = max(maxo, o);
+        if (e) e[2 + j] = v.jmp ? o * (4 * v.tp + 4) : o;
+      }
+      const int nl = max(v.tp / 4 + 1, (v.tp + maxo + 3) / 4);
+      if (e) {
+        for (int j = 2 + v.dpw; j < WI; ++j) e[j] = 0;
+        e[0] = ws;
+        e[1] = nl;
+      }
+      // full-window variants read all nwin samples of every row
+      need = max(need, ws + 63 * v.tp + (v.jmp == 2 ? v.nwin : 4 * nl));
+    } else if (v.kind == KIND_LANE_F32) {
+      for (int j = 0; j < v.dpw; ++j) {
+        const int o = d(w * v.dpw + j) - sbase;
+        if (o > v.rowcap) return kTablesRow;
+        if (e) e[j] = 4 * (c % v.cc * v.rowcap + o);  // byte offset in the pass's buffer
+        need = max(need, o + 64 * v.tp);
+      }
+    } else {
+      uint32_t packed[4] = {0, 0, 0, 0};
+      for (int j = 0; j < v.dpw; ++j) {
+        const int o = d(w * v.dpw + j) - sbase;
+        if (o > 65535) return kTablesOffset;
+        if (v.mode == 0)
+          packed[j >> 1] |= (uint32_t)o << (16 * (j & 1));
+        else if (e)
+          // byte offset into the staged copies: copy o & 3, row slot c % cc, dword o >> 2
+          e[j] = 4 * (((o & 3) * v.cc + c % v.cc) * (v.rowcap / 4) + (o >> 2));
+        need = max(need, (o & ~3) + 256 * v.tp + 4);
+      }
+      if (e && v.mode == 0)
+        for (int j = 0; j < WI; ++j) e[j] = (int32_t)packed[j];
+      else if (e)
+        for (int j = v.dpw; j < WI; ++j) e[j] = 0;
+    }
+  }
+  const int unit = v.kind == KIND_TILE_U8 ? 16 : 4;
+  need = (need + unit - 1) / unit * unit;
+  if (need > v.rowcap) return kTablesRow;
+  if (blk) {
+    blk[((size_t)rt * rows_in + c) * 2 + 0] = sbase;
+    blk[((size_t)rt * rows_in + c) * 2 + 1] = need;
+  }
+  return 0;
+}
+
+__global__ __launch_bounds__(256) void build_tables_kernel(Variant v, DelayView delay, int rows_out, int rows_in,
+                                                           int32_t* __restrict__ blk, int32_t* __restrict__ wav) {
+  const int ncb = (rows_in + 255) / 256;
+  const int rt = blockIdx.x / ncb;
+  const int c = (blockIdx.x - rt * ncb) * 256 + threadIdx.x;
+  if (c < rows_in) (void)table_column(v, delay, rows_out, rows_in, rt, c, blk, wav);
+}
+
+// Whether the variants fit: bad[k] (zero before) becomes the reason if variant k does not.
+struct VariantList {
+  Variant v[kFitBatch];
+};
+__global__ __launch_bounds__(256) void check_fits_kernel(VariantList list, DelayView delay, int rows_out, int rows_in,
+                                                         int* bad) {
+  const Variant& v = list.v[blockIdx.y];
+  const int ncb = (rows_in + 255) / 256;
+  const int rt = blockIdx.x / ncb;
+  const int c = (blockIdx.x - rt * ncb) * 256 + threadIdx.x;
+  if (c >= rows_in || rt * v.dt() >= rows_out) return;
+  const int why = table_column(v, delay, rows_out, rows_in, rt, c, nullptr, nullptr);
+  if (why) atomicMax(bad + blockIdx.y, why);
+}
+
+// Adjoint: per (row tile, pass) the least start and greatest end of the
+// pass's staged windows.
+__global__ __launch_bounds__(256) void build_span_kernel(const int32_t* __restrict__ blk, int rows_in, int cc, int npass,
+                                                         int32_t* __restrict__ span) {
+  const int nqb = (npass + 255) / 256;
+  const int rt = blockIdx.x / nqb;
+  const int q = (blockIdx.x - rt * nqb) * 256 + threadIdx.x;
+  if (q >= npass) return;
+  int smin = INT32_MAX, emax = INT32_MIN;
+  for (int c = q * cc; c < min(rows_in, (q + 1) * cc); ++c) {
+    const int32_t* b = blk + ((size_t)rt * rows_in + c) * 2;
+    smin = min(smin, b[0]);
+    emax = max(emax, b[0] + b[1]);
+  }
+  span[((size_t)rt * npass + q) * 2 + 0] = smin;
+  span[((size_t)rt * npass + q) * 2 + 1] = emax;
+}
+
+}  // namespace
+
+hipError_t launch_build_tables(const Variant& v, const int32_t* d_delay, int nchan, int ndm, bool adjoint, int pad,
+                               int32_t* blk, int32_t* wav, int32_t* span, hipStream_t s) {
+  const int rows_out = adjoint ? nchan : ndm, rows_in = adjoint ? ndm : nchan;
+  const int64_t nrt = (rows_out + v.dt() - 1) / v.dt();
+  const int64_t grid = nrt * ((rows_in + 255) / 256);
+  if (grid > 0x7fffffff) return hipErrorInvalidConfiguration;
+  hipLaunchKernelGGL(build_tables_kernel, dim3((unsigned)grid), dim3(256), 0, s, v,
+                     DelayView{d_delay, nchan, adjoint, pad}, rows_out, rows_in, blk, wav);
+  hipError_t e = hipGetLastError();
+  if (e == hipSuccess && span) {
+    const int npass = (rows_in + v.cc - 1) / v.cc;
+    hipLaunchKernelGGL(build_span_kernel, dim3((unsigned)(nrt * ((npass + 255) / 256))), dim3(256), 0, s, blk, rows_in,
+                       v.cc, npass, span);
+    e = hipGetLastError();
+  }
+  return e;
+}
+
+hipError_t launch_check_fits(const std::vector<const Variant*>& vs, const int32_t* d_delay, int nchan, int ndm,
+                             bool adjoint, int pad, int* bad, hipStream_t s) {
+  if (vs.empty() || vs.size() > kFitBatch) return hipErrorInvalidValue;
+  const int rows_out = adjoint ? nchan : ndm, rows_in = adjoint ? ndm : nchan;
+  VariantList list = {};
+  int64_t nrt = 1;
+  for (size_t k = 0; k < vs.size(); ++k) {
+    list.v[k] = *vs[k];
+    nrt = std::max<int64_t>(nrt, (rows_out + vs[k]->dt() - 1) / vs[k]->dt());
+  }
+  const int64_t grid = nrt * ((rows_in + 255) / 256);
+  if (grid > 0x7fffffff) return hipErrorInvalidConfiguration;
+  hipError_t e = hipMemsetAsync(bad, 0, vs.size() * sizeof(int), s);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(check_fits_kernel, dim3((unsigned)grid, (unsigned)vs.size()), dim3(256), 0, s, list,
+                     DelayView{d_delay, nchan, adjoint, pad}, rows_out, rows_in, bad);
+  return hipGetLastError();
+}
+
+}  // namespace dd

@@ -181,6 +181,7 @@ dedisp_status dedisp_autotune(dedisp_plan p, int32_t nbeam, int32_t nsamp, dedis
   times.assign(vs.size() + 1, -1.f);
   const int saved = u8 ? p->var_u8 : p->var_f32;
   const int dir = u8 ? 1 : 0;
+  const bool by_size = p->by_size[dir];
   auto time_variant = [&](int vi, int reps) {
     if (dedisp_plan_set_variant(p, t, vi) != DEDISP_OK) return -1.f;
     return median_ms(
@@ -220,6 +221,7 @@ dedisp_status dedisp_autotune(dedisp_plan p, int32_t nbeam, int32_t nsamp, dedis
   (void)hipFree(d_out);
   if (best == -2) {
     (void)dedisp_plan_set_variant(p, t, saved);
+    p->by_size[dir] = by_size;
     return fail(DEDISP_E_UNTUNED, "no variant ran");
   }
   dedisp_status st = dedisp_plan_set_variant(p, t, best);
@@ -261,6 +263,7 @@ dedisp_status dedisp_autotune_adjoint(dedisp_plan p, int32_t nbeam, int32_t nsam
   (void)hipEventCreate(&e0);
   (void)hipEventCreate(&e1);
   const int saved = p->var_adj;
+  const bool by_size = p->by_size[2];
   std::vector<float> times(vs.size() + 1, -1.f);
   auto time_variant = [&](int vi, int reps) {
     if (dedisp_plan_set_adjoint_variant(p, vi) != DEDISP_OK) return -1.f;
@@ -301,6 +304,7 @@ dedisp_status dedisp_autotune_adjoint(dedisp_plan p, int32_t nbeam, int32_t nsam
     for (int32_t i = 0; i < n && i <= (int32_t)vs.size(); ++i) ms[i] = times[i];
   if (best == -2) {
     (void)dedisp_plan_set_adjoint_variant(p, saved);
+    p->by_size[2] = by_size;
     return fail(DEDISP_E_UNTUNED, "no adjoint variant ran");
   }
   const dedisp_status st = dedisp_plan_set_adjoint_variant(p, best);
