@@ -275,11 +275,12 @@ dedisp_status dedisp_batch_destroy(dedisp_batch batch);
  *   d_start  [nbeam][ndm] int32         d_mean, d_std [nbeam][ndm] double, or NULL
  *   d_workspace: device scratch of at least dedisp_detect_workspace_bytes(...)
  *            bytes, 16-byte aligned (contents on return: undefined).
- * Uses a kernel variant with the search in its epilogue: the one set with
- * dedisp_plan_set_detect_variant or kept by dedisp_detect_autotune, else the
- * first that fits from an order of preference measured on MI355X (see
- * dedisp_detect_variant); when that is -1 or none fits it dedisperses into
- * the workspace and searches the stored rows (dedisp_detect_rows).  The
+ * Uses the path set with dedisp_plan_set_detect_variant or kept by
+ * dedisp_detect_autotune; else uint8 input takes the first variant with the
+ * search in its epilogue that fits from an order of preference measured on
+ * MI355X (see dedisp_detect_variant), and float32 input, or uint8 input that
+ * none fits, dedisperses into the workspace and searches the stored rows, some
+ * beams at a time (their series take at most 1 GiB, or one beam's).  The
  * forward variant (dedisp_plan_set_variant, dedisp_autotune) only serves the
  * unfused path.  Asynchronous on
  * `stream`; the first call of a plan and dtype may build tile tables

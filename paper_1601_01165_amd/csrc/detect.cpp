@@ -3,6 +3,7 @@
 // fused path runs a tile kernel whose epilogue searches the tile instead of
 // storing it, then merges the per-tile records; the unfused path searches
 // stored rows.  The definition is documented with dedisp_detect.
+#include <algorithm>
 #include <string>
 
 #include "internal.h"
@@ -28,23 +29,34 @@ static bool det_fits(dedisp_plan p, bool u8, int vi) {
 }
 
 // The variant of the search for this plan and dtype: the one set or tuned
-// (-1: unfused); otherwise the first that fits from a preference list
-// (fastest first as measured on MI355X with the search fused: FP32 on the
-// 1024-channel, 2048-DM beam, uint8 on the 32-channel, 2048-DM beam), else -1.
+// (-1: unfused), otherwise the automatic choice.
+//   float32: unfused.  Storing the series and searching them costs about 0.05 ms
+//     on the 1024-channel, 2000-DM beam; the fused forms lose more by their
+//     registers and overlapping tiles (1.10 ms unfused, 1.50 ms the best fused).
+//   uint8: the first that fits from a preference list (fastest first on the
+//     32-channel, 2048-DM beam: the int32 series would be 1.64 GB), or with
+//     fewer blocks than CUs the same kernel with half the samples per tile
+//     (29 channels, 131 DM trials, 20,011 samples: 21.9 against 26.9 us).
+static constexpr int kDetSmallTile = 25;  // 32 DMs x 512 of the 32 DMs x 1024 of variant 23
+
 static int det_variant(dedisp_plan p, bool u8) {
   const int set = u8 ? p->var_det_u8 : p->var_det_f32;
   if (set >= -1) return set;
-  auto fits = [&](int vi) { return det_fits(p, u8, vi); };
-  static const int pref_f32[] = {16, 14, 18, 13, 15, 17};
+  if (!u8) return -1;
   static const int pref_u8[] = {23, 14, 25, 27, 16, 15, 12, 17, 18, 20, 13, 21, 19, 24, 26};
-  if (u8) {
-    for (int vi : pref_u8)
-      if (fits(vi)) return vi;
-  } else {
-    for (int vi : pref_f32)
-      if (fits(vi)) return vi;
-  }
+  for (int vi : pref_u8)
+    if (det_fits(p, true, vi)) return vi;
   return -1;
+}
+
+static int det_variant_for(dedisp_plan p, bool u8, int nbeam, int nsamp) {
+  const int vi = det_variant(p, u8);
+  if (!u8 || p->var_det_u8 >= -1 || vi < 0 || vi == kDetSmallTile) return vi;
+  const Variant& v = variants_u8()[vi];
+  const int64_t blocks = (int64_t)((p->ndm + v.dt() - 1) / v.dt()) * ((nsamp + det_step(v) - 1) / det_step(v)) * nbeam;
+  // looked at on the first call whatever its size, so that later ones allocate nothing
+  const bool small = det_fits(p, true, kDetSmallTile);
+  return small && blocks < p->ncu ? kDetSmallTile : vi;
 }
 
 static size_t round_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
@@ -53,9 +65,16 @@ static int64_t rows_tiles(int nsamp) { return (nsamp + kDetRowsStep - 1) / kDetR
 
 static size_t rows_ws(int64_t nrows, int nsamp) { return (size_t)nrows * rows_tiles(nsamp) * sizeof(DetRec); }
 
-// Unfused fallback: forward into the workspace, then the row search.
+// Unfused path: the forward map of some beams into the workspace, then the row
+// search.  Beams go through it in groups whose series take at most 1 GiB (one
+// beam at least), so the workspace does not grow with their number.
+static int unfused_beams(dedisp_plan p, int nbeam, int nsamp) {
+  const size_t one = (size_t)p->ndm * round_up(nsamp, 4) * 4;
+  return (int)std::max<size_t>(1, std::min<size_t>(nbeam, ((size_t)1 << 30) / one));
+}
+
 static size_t fallback_ws(dedisp_plan p, int nbeam, int nsamp) {
-  const int64_t nrows = (int64_t)nbeam * p->ndm;
+  const int64_t nrows = (int64_t)unfused_beams(p, nbeam, nsamp) * p->ndm;
   const size_t rows = round_up((size_t)nrows * round_up(nsamp, 4) * 4, 256);
   return rows + rows_ws(nrows, nsamp);
 }
@@ -69,7 +88,7 @@ extern "C" {
 size_t dedisp_detect_workspace_bytes(dedisp_plan p, dedisp_dtype in_type, int32_t nbeam, int32_t nsamp) {
   if (!p || nbeam < 1 || nsamp < 1 || (in_type != DEDISP_F32 && in_type != DEDISP_U8)) return 0;
   const bool u8 = in_type == DEDISP_U8;
-  const int vi = det_variant(p, u8);
+  const int vi = det_variant_for(p, u8, nbeam, nsamp);
   if (vi < 0) return fallback_ws(p, nbeam, nsamp);
   const Variant& v = (u8 ? variants_u8() : variants_f32())[vi];
   const int64_t ntiles = (nsamp + det_step(v) - 1) / det_step(v);
@@ -114,24 +133,25 @@ dedisp_status dedisp_detect(dedisp_plan p, int32_t nbeam, int32_t nsamp, const v
   hipStream_t s = (hipStream_t)stream;
   const int64_t nseries = (int64_t)nbeam * p->ndm;
   if (nseries > 0x7ffffff0) return fail(DEDISP_E_SHAPE, "too many series");
-  const int vi = det_variant(p, u8);
+  const int vi = det_variant_for(p, u8, nbeam, nsamp);
   hipError_t e;
   if (vi < 0) {
-    // unfused (no variant with the search in its epilogue fits, or the
-    // unfused path was set or tuned): dedisperse into the workspace, then
-    // search the stored rows
     const int64_t stride = round_up(nsamp, 4);
+    const int step = unfused_beams(p, nbeam, nsamp);
     void* rows = d_ws;
-    DetRec* recs = (DetRec*)((char*)d_ws + round_up((size_t)nseries * stride * 4, 256));
-    st = dedisp_execute(p, nbeam, nsamp, d_in, in_type, in_stride, d_w, rows, u8 ? DEDISP_I32 : DEDISP_F32, stride,
-                        stream);
-    if (st != DEDISP_OK) return st;
+    DetRec* recs = (DetRec*)((char*)d_ws + round_up((size_t)step * p->ndm * stride * 4, 256));
     const int ntiles = (int)rows_tiles(nsamp);
-    e = launch_detect_rows(rows, u8, stride, (int)nseries, nsamp, ntiles, recs, s);
-    if (e != hipSuccess) return hip_fail(e, "launching the row search");
-    e = launch_det_finish(recs, false, (int)nseries, ntiles, nsamp, nwidth, d_snr, d_width, d_start, d_mean, d_std,
-                          s);
-    return e == hipSuccess ? DEDISP_OK : hip_fail(e, "launching the record merge");
+    for (int b = 0; b < nbeam; b += step) {
+      const int nb = std::min(step, nbeam - b);
+      const int64_t s0 = (int64_t)b * p->ndm;
+      st = dedisp_execute(p, nb, nsamp, (const char*)d_in + (int64_t)b * p->nchan * in_stride * esz, in_type, in_stride,
+                          d_w, rows, u8 ? DEDISP_I32 : DEDISP_F32, stride, stream);
+      if (st != DEDISP_OK) return st;
+      e = launch_detect_rows(rows, u8, stride, nb * p->ndm, nsamp, ntiles, nwidth, recs, d_snr + s0, d_width + s0,
+                             d_start + s0, d_mean ? d_mean + s0 : nullptr, d_std ? d_std + s0 : nullptr, s);
+      if (e != hipSuccess) return hip_fail(e, "launching the row search");
+    }
+    return DEDISP_OK;
   }
   Tables* t = nullptr;
   st = ensure_tables(p, u8 ? 1 : 0, vi, &t);
@@ -274,10 +294,9 @@ dedisp_status dedisp_detect_rows(int32_t nrows, int32_t nsamp, const void* d_row
   hipStream_t s = (hipStream_t)stream;
   const int ntiles = (int)rows_tiles(nsamp);
   DetRec* recs = (DetRec*)d_ws;
-  hipError_t e = launch_detect_rows(d_rows, type == DEDISP_I32, stride, nrows, nsamp, ntiles, recs, s);
-  if (e != hipSuccess) return hip_fail(e, "launching the row search");
-  e = launch_det_finish(recs, false, nrows, ntiles, nsamp, nwidth, d_snr, d_width, d_start, d_mean, d_std, s);
-  return e == hipSuccess ? DEDISP_OK : hip_fail(e, "launching the record merge");
+  const hipError_t e = launch_detect_rows(d_rows, type == DEDISP_I32, stride, nrows, nsamp, ntiles, nwidth, recs, d_snr,
+                                          d_width, d_start, d_mean, d_std, s);
+  return e == hipSuccess ? DEDISP_OK : hip_fail(e, "launching the row search");
 }
 
 }  // extern "C"

@@ -183,8 +183,10 @@ hipError_t launch_detect(const Variant& v, const TileArgs& a, int nbeam, hipStre
 constexpr int kDetRowsRun = 16;                              // starts per lane
 constexpr int kDetRowsTile = 64 * kDetRowsRun;               // samples per tile
 constexpr int kDetRowsStep = kDetRowsTile - 2 * kDetRowsRun;  // owned starts per tile
-hipError_t launch_detect_rows(const void* rows, bool i32, int64_t stride, int nrows, int nsamp, int ntiles,
-                              DetRec* recs, hipStream_t s);
+// recs: room for nrows x ntiles records.
+hipError_t launch_detect_rows(const void* rows, bool i32, int64_t stride, int nrows, int nsamp, int ntiles, int nwidth,
+                              DetRec* recs, double* snr, int32_t* width, int32_t* start, double* mean, double* stdv,
+                              hipStream_t s);
 // Merge the records of each series (tile order) into its result.
 hipError_t launch_det_finish(const DetRec* recs, bool int_vals, int nseries, int ntiles, int nsamp, int nwidth,
                              double* snr, int32_t* width, int32_t* start, double* mean, double* stdv, hipStream_t s);

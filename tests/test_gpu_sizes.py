@@ -45,10 +45,11 @@ def test_forward_choice_by_size(nc, nd, step, weighted):
         assert np.array_equal(got, oracle.forward_f32(x, delta, ns, w)), (nb, ns)
 
 
-@pytest.mark.parametrize("nc,nd,step", [(5, 3, 0.25), (40, 70, 0.25), (12, 90, 1.0), (33, 41, 4.0)])
+@pytest.mark.parametrize("nc,nd,step", [(5, 3, 0.25), (40, 70, 0.25), (60, 80, 0.5), (12, 90, 1.0), (33, 41, 4.0)])
 def test_adjoint_choice_and_wide_spans(nc, nd, step):
     """The untuned adjoint at several sizes, then every variant that fits (the
-    wide register windows and the lane kernels take spans the others refuse)."""
+    wide register windows and the lane kernels take spans the others refuse; the
+    last two set-ups are too wide for any tile and run the direct kernel)."""
     dd = _dd()
     rng = np.random.default_rng(3 * nc + nd)
     f, dms, delta = _setup(nc, nd, step)
@@ -72,7 +73,9 @@ def test_adjoint_choice_and_wide_spans(nc, nd, step):
             assert np.array_equal(gi.cpu().numpy(), oracle.adjoint_gather_f32(g, delta, nin, w)), (v, nb, ns)
             ref, scale = oracle.grad_w(x, g, delta)
             assert (np.abs(gw.cpu().numpy() - ref) <= 1e-5 * scale + 1e-6 * np.abs(ref)).all(), (v, nb, ns)
-    assert None in seen and len(seen) > 1
+    assert None in seen
+    if (nc, nd) == (60, 80):
+        assert {39, 40} <= seen, seen  # up to 17 samples between neighbouring channels
 
 
 @pytest.mark.parametrize("nc,nd", [(3, 5), (40, 33), (300, 70)])
