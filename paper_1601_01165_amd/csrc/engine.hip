@@ -84,13 +84,23 @@ __global__ __launch_bounds__(256) void direct_adjoint_kernel(const float* __rest
   }
 }
 
-// grad_w[c] = sum over parts p (ascending) of partial[p][c].
-__global__ __launch_bounds__(256) void reduce_gradw_kernel(const double* __restrict__ partial, int nparts, int nchan,
-                                                           float* grad_w) {
-  const int c = blockIdx.x * 256 + threadIdx.x;
-  if (c >= nchan) return;
+// grad_w[c] = sum over parts p of partial[p][c], in FP64 and in a fixed order:
+// thread row y of a block sums parts y, y + 32, ... of 32 channels, then the 32
+// rows' sums are added in order: a short chain of loads whatever the number of
+// parts (beams x time tiles).
+constexpr int kGradwRows = 32, kGradwChans = 32;
+__global__ __launch_bounds__(kGradwRows* kGradwChans) void reduce_gradw_kernel(const double* __restrict__ partial,
+                                                                               int nparts, int nchan, float* grad_w) {
+  __shared__ double sums[kGradwRows][kGradwChans];
+  const int x = threadIdx.x % kGradwChans, y = threadIdx.x / kGradwChans;
+  const int c = blockIdx.x * kGradwChans + x;
   double s = 0.0;
-  for (int p = 0; p < nparts; ++p) s += partial[(size_t)p * nchan + c];
+  if (c < nchan)
+    for (int p = y; p < nparts; p += kGradwRows) s += partial[(size_t)p * nchan + c];
+  sums[y][x] = s;
+  __syncthreads();
+  if (y != 0 || c >= nchan) return;
+  for (int k = 1; k < kGradwRows; ++k) s += sums[k][x];
   grad_w[c] = (float)s;
 }
 
@@ -220,7 +230,8 @@ hipError_t launch_direct_adjoint(const float* g, int64_t g_stride, int64_t g_bea
 }
 
 hipError_t launch_reduce_gradw(const double* partial, int nparts, int nchan, float* grad_w, hipStream_t s) {
-  hipLaunchKernelGGL(reduce_gradw_kernel, dim3((nchan + 255) / 256), dim3(256), 0, s, partial, nparts, nchan, grad_w);
+  hipLaunchKernelGGL(reduce_gradw_kernel, dim3((nchan + kGradwChans - 1) / kGradwChans), dim3(kGradwRows * kGradwChans), 0,
+                     s, partial, nparts, nchan, grad_w);
   return hipGetLastError();
 }
 
