@@ -47,14 +47,28 @@ struct Variant {
   // 256 input rows); 2 = as 1, flushed to int32 sums every 256 rows; 3 = four copies, summed by the matrix cores
   int mode = 0;
   // f32 only: 1 = each row's DM slots branch into static blocks of adds; the table then holds block byte
-  // offsets o * (4 * tp + 4) in place of the window offsets o
+  // offsets o * (4 * tp + 4) in place of the window offsets o; 2 = the same reading the whole window; 3 = one
+  // block of code per row
   int jmp = 0;
+  // f32, row blocks (jmp 3; gen_win_asm.py row_pass): block (m, p, o) of the code region, for offsets o,
+  // o + d1, ... whose differences are m plus the bits of p (p < 7, m < row_classes, o < 4)
+  static constexpr int kRowStub = 512;
+  static __host__ __device__ constexpr int row_block_bytes(int tp, int nwin) { return 16 * tp + 2 * nwin + 56; }
+  __host__ __device__ int row_classes() const { return (nwin - tp - 5) / 3 + 1; }
+  __host__ __device__ int row_block(int m, int p, int o) const {
+    return kRowStub + ((m * 7 + p) * 4 + o) * row_block_bytes(tp, nwin);
+  }
+  // f32: the jump form that reads the next row's window while the last slot adds, and the stride of
+  // that slot's blocks (the adds, the jump and one 8-byte read instruction per 4 window registers)
+  __host__ __device__ bool prefetch() const { return kind == KIND_WIN_F32 && jmp == 1 && dpw == 4; }
+  __host__ __device__ int last_stride() const { return 4 * tp + 4 + 2 * nwin; }
   __host__ __device__ int st() const { return kind == KIND_TILE_U8 ? 256 * tp : 64 * tp; }
   __host__ __device__ int dt() const { return nwave * dpw; }
   // ints per wave-table entry: f32 {win_start, nl, one offset per row} padded to 4/8/16; u8 packed u16
   // offsets (mode 0) or one LDS byte offset per row (byte-shifted modes)
   __host__ __device__ int wav_ints() const {
     if (kind == KIND_LANE_F32) return dpw;  // one LDS byte offset per row
+    if (jmp == 3) return 4;  // row blocks: {window start in bytes, block, packed offsets, reads and flags}
     if (kind == KIND_WIN_F32) return dpw + 2 <= 4 ? 4 : dpw + 2 <= 8 ? 8 : 16;
     return mode == 0 ? 4 : (dpw <= 4 ? 4 : 8);
   }

@@ -216,10 +216,10 @@ struct SizeCost {
   float alone, full;
 };
 static const std::vector<SizeCost>& size_costs(int dir) {
-  static const std::vector<SizeCost> f32 = {{35, .47f, .508f}, {41, .100f, .036f}, {42, .132f, .061f}};
+  static const std::vector<SizeCost> f32 = {{35, .45f, .478f}, {41, .100f, .036f}, {42, .132f, .061f}};
   static const std::vector<SizeCost> u8 = {{22, .50f, .51f},  {23, .27f, .207f},
                                            {25, .18f, .125f}, {26, .13f, .079f}, {27, .14f, .150f}};
-  static const std::vector<SizeCost> adj = {{37, .47f, .508f}, {39, .50f, .500f}, {41, .100f, .036f}, {43, .178f, .125f}};
+  static const std::vector<SizeCost> adj = {{37, .45f, .478f}, {39, .50f, .500f}, {41, .100f, .036f}, {43, .178f, .125f}};
   return dir == 1 ? u8 : dir == 2 ? adj : f32;
 }
 

@@ -39,17 +39,66 @@ __device__ int table_column(const Variant& v, const DelayView& delay, int rows_o
       const int ws = (wmin - sbase) & ~3;
       if (ws > v.rowcap) return kTablesRow;
       int maxo = 0;
+      if (v.jmp == 3) {
+        // row blocks: the offsets' pattern if it has a block, else the slots (target 0)
+        int m = INT32_MAX, top = 0, prev = 0, p = 0, packed = 0;
+        for (int j = 0; j < v.dpw; ++j) {
+          const int o = d(w * v.dpw + j) - sbase - ws;
+          if (o < 0 || o > v.nwin - v.tp) return kTablesWindow;
+          maxo = max(maxo, o);
+          packed |= o << (8 * j);
+          if (j > 0) {
+            m = min(m, o - prev);
+            top = max(top, o - prev);
+          }
+          prev = o;
+        }
+        const int nl = max(v.tp / 4 + 1, (v.tp + maxo + 3) / 4);
+        need = max(need, ws + 63 * v.tp + 4 * nl);
+        if (!e) continue;
+        const bool last = c % v.cc == v.cc - 1 || c == rows_in - 1;
+        const int o0 = packed & 0xff;
+        int target = 0;
+        if (!last && m >= 0 && top - m <= 1 && m < v.row_classes() && o0 < 4) {
+          for (int j = 1; j < v.dpw; ++j)
+            p |= ((packed >> (8 * j) & 0xff) - (packed >> (8 * j - 8) & 0xff) - m) << (j - 1);
+          target = v.row_block(m, p, o0);
+        }
+        // reads beyond those the row before asks for (as many as its last offset needs)
+        int extra = 0;
+        if (c > 0) {
+          auto d1 = [&](int j) { return delay(min(rt * DT + w * v.dpw + j, rows_out - 1), c - 1); };
+          int pmin = d1(0);
+          for (int j = 1; j < v.dpw; ++j) pmin = min(pmin, d1(j));
+          const int olast = d1(v.dpw - 1) - (pmin & ~3);
+          if (nl > min(v.nwin / 4, max(v.tp / 4 + 1, (v.tp + olast + 3) / 4))) extra = nl;
+        }
+        e[0] = 4 * ws;
+        e[1] = target;
+        e[2] = packed;
+        e[3] = nl | extra << 8 | (last ? 0 : (int)0x80000000u);
+        continue;
+      }
       for (int j = 0; j < v.dpw; ++j) {
         const int o = d(w * v.dpw + j) - sbase - ws;
         if (o < 0 || o > v.nwin - v.tp) return kTablesWindow;
         maxo = max(maxo, o);
-        if (e) e[2 + j] = v.jmp ? o * (4 * v.tp + 4) : o;
+        if (e) e[2 + j] = v.jmp ? o * (v.prefetch() && j == v.dpw - 1 ? v.last_stride() : 4 * v.tp + 4) : o;
       }
       const int nl = max(v.tp / 4 + 1, (v.tp + maxo + 3) / 4);
       if (e) {
         for (int j = 2 + v.dpw; j < WI; ++j) e[j] = 0;
         e[0] = ws;
         e[1] = nl;
+        if (v.prefetch() && c > 0) {
+          // reads beyond those the row before already asked for (as many as its last slot needed)
+          auto d1 = [&](int j) { return delay(min(rt * DT + w * v.dpw + j, rows_out - 1), c - 1); };
+          int pmin = d1(0);
+          for (int j = 1; j < v.dpw; ++j) pmin = min(pmin, d1(j));
+          const int olast = d1(v.dpw - 1) - (pmin & ~3);
+          const int asked = min(v.nwin / 4, max(v.tp / 4 + 1, (v.tp + olast + 3) / 4));
+          e[6] = nl > asked ? nl : 0;
+        }
       }
       // full-window variants read all nwin samples of every row
       need = max(need, ws + 63 * v.tp + (v.jmp == 2 ? v.nwin : 4 * nl));

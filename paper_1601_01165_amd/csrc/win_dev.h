@@ -16,8 +16,10 @@
 //   * each wave owns dpw output rows and 64*tp samples, each lane tp
 //     consecutive samples.  Per input row the lane copies its window of
 //     samples from LDS into registers once (16-byte LDS reads) and every one
-//     of its dpw rows adds tp window registers, selected through VGPR index
-//     mode with the row's delay offset (see gen_win_asm.py).  One LDS byte
+//     of its dpw rows adds the tp window registers that start at the row's
+//     delay offset, selected by jumping into static code: a block per row for
+//     regular DM lists, one per output row, or through VGPR index mode (see
+//     gen_win_asm.py).  One LDS byte
 //     thus feeds several adds, which is what keeps the add units busy: an LDS
 //     read per add would cap the rate at the LDS bandwidth.
 //   * blocks are remapped so that the blocks of one time tile run on the same
@@ -304,7 +306,11 @@ __device__ __forceinline__ void win_tile(int wave, const TileArgs& a, int tt, in
   constexpr int ST = 64 * TP;
   constexpr int DT = NWAVE * DPW;
   constexpr int NACC = TP * DPW / 16;
-  constexpr int WI = EntT<DPW>::ints;
+  constexpr bool RB = JMP == 3;  // one block of code per row
+  static_assert(!RB || has_row_pass(TP, DPW, NWIN, JmpAcc0<TP, DPW, NWIN, CC>::value), "no row blocks for this shape");
+  static_assert(Variant::kRowStub == kGenRowStub && Variant::row_block_bytes(TP, NWIN) == gen_row_block(TP, NWIN),
+                "the tables' block offsets are not the generated code's");
+  constexpr int WI = RB ? 4 : EntT<DPW>::ints;
   tt = __builtin_amdgcn_readfirstlane(tt);
   rt = __builtin_amdgcn_readfirstlane(rt);
   const int t0 = DET ? tt * a.tile_step : tt * ST;
@@ -323,12 +329,15 @@ __device__ __forceinline__ void win_tile(int wave, const TileArgs& a, int tt, in
   // step fetches the next row's through a buffer resource (reads past the
   // last row return zero), advancing the byte offset itself.  Weights were
   // applied when the rows were staged, so the steps only add.
-  typedef typename EntT<DPW>::type E;
+  typedef typename std::conditional<RB, ent4_t, typename EntT<DPW>::type>::type E;
   const __amdgpu_buffer_rsrc_t trs =
       __builtin_amdgcn_make_buffer_rsrc((void*)wav, (short)0, a.rows_in * WI * 4, 0x00020000);
   const __amdgpu_buffer_rsrc_t wrs = __builtin_amdgcn_make_buffer_rsrc(nullptr, (short)0, 0, 0x00020000);
-  uint32_t toff = WI * 4, woff = 4;
+  // the prefetching jump form holds two entries, the others load one ahead
+  constexpr bool PF = JMP == 1 && DPW == 4;
+  uint32_t toff = (PF ? 2 : 1) * WI * 4, woff = 4;
   E ea = sload_entry_t<E>(wav), eb;
+  if (PF) eb = sbload_t<E>(trs, WI * 4);
   float wa = 0.f, wb = 0.f;
   const int npass = (a.rows_in + CC - 1) / CC;
   int32_t stg = 0;      // staging entries (and weights) of the next pass (NBUF = 2)
@@ -348,8 +357,9 @@ __device__ __forceinline__ void win_tile(int wave, const TileArgs& a, int tt, in
       while (p_lo <= p_hi && !live(p_lo)) ++p_lo;
       while (p_hi > p_lo && !live(p_hi)) --p_hi;
       if (p_lo > 0) {
-        toff = (uint32_t)((p_lo * CC + 1) * WI * 4);
+        toff = (uint32_t)((p_lo * CC + (PF ? 2 : 1)) * WI * 4);
         ea = sbload_t<E>(trs, (uint32_t)(p_lo * CC * WI * 4));
+        if (PF) eb = sbload_t<E>(trs, (uint32_t)((p_lo * CC + 1) * WI * 4));
       }
     }
   }
@@ -381,10 +391,16 @@ __device__ __forceinline__ void win_tile(int wave, const TileArgs& a, int tt, in
     }
     // LDS byte address of this lane's window in the pass's first row slot
     uint32_t row = lds_base + (uint32_t)(lane_fresh() * TP * 4) + (uint32_t)(bufrow * ROWCAP * 4);
-    if constexpr (JMP) {
+    if constexpr (RB) {
+      // the rows of the pass, block by block; the table marks the last one
+      RowPass<TP, DPW, NWIN, ROWCAP>::run(acc, row, ea, trs, toff);
+    } else if constexpr (JMP) {
       // the whole pass in one block, each row's DM slots branching into static adds
       static_assert(HasJmpPass<TP, DPW, NWIN, CC>::value, "no jump-form pass for this shape");
-      JmpPass<TP, DPW, NWIN, CC, false, JMP == 2, ROWCAP>::run(acc, row, ncc, ea, trs, toff, wa, wrs, woff);
+      if constexpr (PF)
+        JmpPrefetchPass<TP, DPW, NWIN, CC, ROWCAP>::run(acc, row, ncc, ea, eb, trs, toff);
+      else
+        JmpPass<TP, DPW, NWIN, CC, false, JMP == 2, ROWCAP>::run(acc, row, ncc, ea, trs, toff, wa, wrs, woff);
     } else if constexpr (HasWinPass<TP, DPW, NWIN, CC>::value) {
       // the whole pass in one block, index mode on throughout
       WinPass<TP, DPW, NWIN, CC, false, ROWCAP>::run(acc, row, ncc, ea, trs, toff, wa, wrs, woff);
@@ -520,13 +536,13 @@ void win_persistent(const BeamDesc* __restrict__ beams,
   X(29, 20, 4, 12, 44, 4, 1792, 2, 2) /* 48 DMs x 1280, jump full */ \
   X(30, 20, 4, 4, 44, 4, 1536, 2, 2)  /* 16 DMs x 1280, jump full */ \
   X(31, 20, 8, 8, 56, 4, 1792, 2, 2)  /* 64 DMs x 1280, jump full */ \
-  X(32, 20, 4, 8, 40, 6, 1536, 2, 1)  /* 32 DMs x 1280, jump, 4 waves/SIMD */ \
-  X(33, 20, 4, 4, 40, 3, 1536, 2, 1)  /* 16 DMs x 1280, jump, 4 waves/SIMD */ \
-  X(34, 20, 4, 16, 40, 8, 1792, 2, 1) /* 64 DMs x 1280, jump, 4 waves/SIMD */ \
-  X(35, 20, 4, 16, 40, 10, 1792, 2, 1) /* 64 DMs x 1280, jump, 4 waves/SIMD */ \
+  X(32, 20, 4, 8, 40, 6, 1536, 2, 3)  /* 32 DMs x 1280, row blocks, 4 waves/SIMD */ \
+  X(33, 20, 4, 4, 40, 3, 1536, 2, 3)  /* 16 DMs x 1280, row blocks, 4 waves/SIMD */ \
+  X(34, 20, 4, 16, 40, 8, 1792, 2, 3) /* 64 DMs x 1280, row blocks, 4 waves/SIMD */ \
+  X(35, 20, 4, 16, 40, 10, 1792, 2, 3) /* 64 DMs x 1280, row blocks, 4 waves/SIMD */ \
   X(36, 20, 4, 16, 40, 8, 1792, 2, 2) /* 64 DMs x 1280, jump full, 4 waves/SIMD */ \
-  X(37, 20, 4, 16, 44, 10, 1792, 2, 1) /* 64 DMs x 1280, jump, 4 waves/SIMD */ \
-  X(38, 20, 4, 16, 44, 8, 1792, 2, 1) /* 64 DMs x 1280, jump, 4 waves/SIMD */ \
+  X(37, 20, 4, 16, 44, 10, 1792, 2, 3) /* 64 DMs x 1280, row blocks, 4 waves/SIMD */ \
+  X(38, 20, 4, 16, 44, 8, 1792, 2, 3) /* 64 DMs x 1280, row blocks, 4 waves/SIMD */ \
   X(39, 20, 4, 12, 84, 8, 2304, 2, 1) /* 48 DMs x 1280, jump, wide spans, 3 waves/SIMD */ \
   X(40, 20, 4, 4, 84, 3, 1792, 2, 1)  /* 16 DMs x 1280, jump, wide spans, 3 waves/SIMD */
 
