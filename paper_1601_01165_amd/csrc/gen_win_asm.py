@@ -801,6 +801,7 @@ def row_pass(tp, dpw, nwin, acc0):
 ROW_SHAPES = [
     (20, 4, 40, 8),
     (20, 4, 44, 4),
+    (12, 4, 32, 8),
 ]
 
 
@@ -819,6 +820,7 @@ JMP_VARIANTS = [
     (20, 4, 44, 10, 4),
     (20, 4, 84, 8, 4),
     (20, 4, 84, 3, 4),
+    (12, 4, 32, 8, 8),
 ]
 
 

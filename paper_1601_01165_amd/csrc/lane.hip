@@ -222,11 +222,11 @@ __global__ __launch_bounds__(64 * NWAVE) void lane_kernel(TileArgs a) {
 
 // (index, Q, DPW, NWAVE, CC rows per pass, ROWCAP floats per row, NBUF)
 #define LANE_VARIANTS(X)                                    \
-  X(43, 1, 1, 8, 8, 384, 4)  /* 8 DMs x 256 */              \
-  X(44, 1, 2, 8, 8, 384, 4)  /* 16 DMs x 256 */             \
-  X(45, 2, 2, 8, 8, 768, 3)  /* 16 DMs x 512 */             \
-  X(46, 2, 1, 8, 8, 640, 4)  /* 8 DMs x 512 */              \
-  X(47, 1, 2, 8, 8, 1024, 3) /* 16 DMs x 256, wide spans */
+  X(44, 1, 1, 8, 8, 384, 4)  /* 8 DMs x 256 */              \
+  X(45, 1, 2, 8, 8, 384, 4)  /* 16 DMs x 256 */             \
+  X(46, 2, 2, 8, 8, 768, 3)  /* 16 DMs x 512 */             \
+  X(47, 2, 1, 8, 8, 640, 4)  /* 8 DMs x 512 */              \
+  X(48, 1, 2, 8, 8, 1024, 3) /* 16 DMs x 256, wide spans */
 
 void lane_variants(std::vector<Variant>& r) {
 #define MAKE_LANE(ID, Q, DPW, NW, CC, RC, NB)                                                                   \

@@ -192,10 +192,10 @@ dedisp_status ensure_tables(dedisp_plan p, int dir, int vi, Tables** out) {
 // 8-sample-per-lane forms took before (2.08 against 5.62 ms).
 const std::vector<int>& default_order(int dir) {
   static const std::vector<int> f32 = {35, 34, 37, 38, 36, 32, 33, 22, 28, 21, 29, 31, 23, 30, 19, 20, 39, 40, 25, 24, 27, 26, 15, 18, 13,
-                                       17, 9,  8,  16, 6,  14, 11, 7,  12, 10, 2,  3,  0,  1,  5,  4,  41, 42, 45, 47, 44, 46, 43};
+                                       17, 9,  8,  16, 6,  14, 11, 7,  12, 10, 2,  3,  0,  1,  5,  4,  41, 42, 43, 46, 48, 45, 47, 44};
   static const std::vector<int> u8 = {22, 23, 25, 27, 26, 24, 16, 20, 15, 21, 12, 13, 17, 14, 18, 6, 2, 0, 5, 19, 9, 3, 4, 1, 8, 7, 10, 11};
   static const std::vector<int> adj = {37, 38, 39, 40, 26, 27, 32, 34, 35, 36, 33, 19, 21, 29, 20, 30, 9, 8, 6, 11, 12, 7, 10, 13, 22, 28,
-                                       18, 15, 23, 31, 17, 16, 25, 24, 14, 2, 3, 1, 0, 5, 4, 42, 41, 45, 46, 44, 47, 43};
+                                       18, 15, 23, 31, 17, 16, 25, 24, 14, 2, 3, 1, 0, 5, 4, 42, 41, 43, 46, 47, 45, 48, 44};
   return dir == 1 ? u8 : dir == 2 ? adj : f32;
 }
 
@@ -212,17 +212,20 @@ const std::vector<int>& default_order(int dir) {
 // 11,790 samples are 170 coarse tiles in 193 us and 315 us in fine ones.  Tiles of
 // 48 DM trials (3 waves per SIMD, 0.85 of the coarse tile's time) take the calls
 // that would leave the last round of coarse tiles half empty (3 beams of 768
-// channels, 1001 DM trials, 9973 samples: 752 against 775 us).  Over 18 random
-// shapes each way the variant chosen is 1 to 2 % from the fastest on average.
+// channels, 1001 DM trials, 9973 samples: 752 against 775 us), and tiles of 32 x
+// 768 those between the sizes (two blocks per CU share one's waits: 2 beams of 264
+// channels, 239 DM trials, 18,314 samples take 106 us, 132 us in coarse tiles and 153
+// in LDS; backward 93, 125 and 170).  Over 18 random shapes each way the variant
+// chosen is 1 % from the fastest on average, and 15 % at most.
 struct SizeCost {
   int vi;
   float alone, full;
 };
 static const std::vector<SizeCost>& size_costs(int dir) {
-  static const std::vector<SizeCost> f32 = {{35, .45f, .478f}, {41, .40f, .405f}, {43, .100f, .036f}, {44, .132f, .061f}};
+  static const std::vector<SizeCost> f32 = {{35, .45f, .478f}, {41, .40f, .405f}, {43, .28f, .195f}, {44, .100f, .036f}, {45, .132f, .061f}};
   static const std::vector<SizeCost> u8 = {{22, .50f, .51f},  {23, .27f, .207f},
                                            {25, .18f, .125f}, {26, .13f, .079f}, {27, .14f, .150f}};
-  static const std::vector<SizeCost> adj = {{37, .45f, .478f}, {42, .40f, .405f}, {39, .44f, .440f}, {43, .100f, .036f}, {45, .178f, .125f}};
+  static const std::vector<SizeCost> adj = {{37, .45f, .478f}, {42, .40f, .405f}, {39, .44f, .440f}, {43, .28f, .195f}, {44, .100f, .036f}, {46, .178f, .125f}};
   return dir == 1 ? u8 : dir == 2 ? adj : f32;
 }
 

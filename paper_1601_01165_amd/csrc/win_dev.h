@@ -546,6 +546,7 @@ void win_persistent(const BeamDesc* __restrict__ beams,
   X(39, 20, 4, 12, 84, 8, 2304, 2, 1) /* 48 DMs x 1280, jump, wide spans, 3 waves/SIMD */ \
   X(40, 20, 4, 4, 84, 3, 1792, 2, 1)  /* 16 DMs x 1280, jump, wide spans, 3 waves/SIMD */ \
   X(41, 20, 4, 12, 40, 10, 1792, 2, 3) /* 48 DMs x 1280, row blocks */ \
-  X(42, 20, 4, 12, 44, 10, 1792, 2, 3) /* 48 DMs x 1280, row blocks */
+  X(42, 20, 4, 12, 44, 10, 1792, 2, 3) /* 48 DMs x 1280, row blocks */ \
+  X(43, 12, 4, 8, 32, 8, 1024, 2, 3) /* 32 DMs x 768, row blocks */
 
 }  // namespace dd
