@@ -158,12 +158,17 @@ hipError_t launch_tiled_u8(const Variant& v, const TileArgs& a, dim3 grid, hipSt
 hipError_t launch_detect_u8(const Variant& v, const TileArgs& a, dim3 grid, hipStream_t s);
 // Lane kernels (lane.hip).
 hipError_t launch_lane(const Variant& v, const TileArgs& a, dim3 grid, bool adjoint, hipStream_t s);
-// Build a variant's tables from the delay matrix [ndm][nchan] (span: adjoint, or
-// null); the variant must fit.
-hipError_t launch_build_tables(const Variant& v, const int32_t* d_delay, int nchan, int ndm, bool adjoint, int pad,
-                               int32_t* blk, int32_t* wav, int32_t* span, hipStream_t s);
-// Whether up to kFitBatch variants fit the delay matrix: bad[k] = 0 or why not.
+// Up to kFitBatch variants' tables built from the delay matrix [ndm][nchan] in one launch
+// (span: adjoint only); the variants must fit.
 constexpr int kFitBatch = 16;
+struct TableBuild {
+  Variant v;
+  int32_t *blk, *wav, *span;
+  size_t ent, slack;  // ints of wav's entries, and zeroed after them
+};
+hipError_t launch_build_tables(const std::vector<TableBuild>& bs, const int32_t* d_delay, int nchan, int ndm,
+                               bool adjoint, int pad, hipStream_t s);
+// Whether up to kFitBatch variants fit the delay matrix: bad[k] = 0 or why not.
 enum { kTablesWindow = 1, kTablesRow = 2, kTablesOffset = 3, kTablesPacked = 4 };
 hipError_t launch_check_fits(const std::vector<const Variant*>& vs, const int32_t* d_delay, int nchan, int ndm,
                              bool adjoint, int pad, int* bad, hipStream_t s);

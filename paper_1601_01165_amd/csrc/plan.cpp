@@ -129,55 +129,58 @@ static dedisp_status check_fits(dedisp_plan p, int dir, const std::vector<int>& 
   return DEDISP_OK;
 }
 
-// Build the tables of variant `vi` in direction `dir`, in memory of their own or
-// from int `at` of `mem`; the build may still be running on the null stream on
-// return.
-static dedisp_status build_tables(dedisp_plan p, int dir, int vi, Tables** out, std::shared_ptr<void> mem, size_t at) {
+// Build the tables of the variants `ids` (each fits, none is built yet) in direction
+// `dir` in one allocation and one launch, complete for every stream on return.
+static dedisp_status build_tables(dedisp_plan p, int dir, const std::vector<int>& ids) {
   std::map<int, Tables>& m = dir == 0 ? p->fwd_f32 : dir == 1 ? p->fwd_u8 : p->adj_f32;
-  auto it = m.find(vi);
-  if (it != m.end()) {
-    if (out) *out = &it->second;
-    return DEDISP_OK;
-  }
   const std::vector<Variant>& vs = dir == 1 ? variants_u8() : variants_f32();
-  if (vi < 0 || vi >= (int)vs.size()) return fail(DEDISP_E_INVALID, "variant index out of range");
-  const dedisp_status st = check_fits(p, dir, {vi});
-  if (st != DEDISP_OK) return st;
-  const Variant& v = vs[vi];
-  static const char* const why[] = {"", "delay span within a wave exceeds the register window",
-                                    "delay span within a block exceeds the LDS row",
-                                    "delay span exceeds the 16-bit offset range",
-                                    "more than 256 input rows overflow its packed sums"};
-  if (p->fits[dir][vi]) return fail(DEDISP_E_UNTUNED, std::string(v.name) + ": " + why[p->fits[dir][vi]]);
-  const TableSizes n = table_sizes(p, dir, v);
-  hipError_t e = mem ? hipSuccess : shared_malloc(mem, n.total() * sizeof(int32_t));
-  Tables t;
-  if (e == hipSuccess) {
+  size_t total = 0, at = 0;
+  for (int vi : ids) total += table_sizes(p, dir, vs[vi]).total();
+  std::shared_ptr<void> mem;
+  hipError_t e = shared_malloc(mem, total * sizeof(int32_t));
+  if (e != hipSuccess) return fail(DEDISP_E_NOMEM, "device allocation of tile tables failed");
+  std::vector<Tables> built;
+  std::vector<TableBuild> bs;
+  for (int vi : ids) {
+    const Variant& v = vs[vi];
+    const TableSizes n = table_sizes(p, dir, v);
+    Tables t;
     t.variant = vi;
     t.n_row_tiles = ((dir == 2 ? p->nchan : p->ndm) + v.dt() - 1) / v.dt();
     t.mem = mem;
     t.d_blk = static_cast<int32_t*>(mem.get()) + at;
     t.d_wav = t.d_blk + n.blk;
     if (n.span) t.d_span = t.d_wav + n.ent + n.slack;
-    e = hipMemsetAsync(t.d_wav + n.ent, 0, n.slack * sizeof(int32_t), nullptr);
+    at += n.total();
+    built.push_back(t);
+    bs.push_back({v, t.d_blk, t.d_wav, t.d_span, n.ent, n.slack});
   }
-  if (e == hipSuccess)
-    e = launch_build_tables(v, p->d_delay, p->nchan, p->ndm, dir == 2, p->adj_pad, t.d_blk, t.d_wav, t.d_span, nullptr);
-  if (e != hipSuccess)
-    return e == hipErrorOutOfMemory ? fail(DEDISP_E_NOMEM, "device allocation of tile tables failed")
-                                    : hip_fail(e, "building tile tables");
-  auto res = m.emplace(vi, t);
-  if (out) *out = &res.first->second;
+  e = launch_build_tables(bs, p->d_delay, p->nchan, p->ndm, dir == 2, p->adj_pad, nullptr);
+  if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
+  if (e != hipSuccess) return hip_fail(e, "building tile tables");
+  for (const Tables& t : built) m.emplace(t.variant, t);
   return DEDISP_OK;
 }
 
 dedisp_status ensure_tables(dedisp_plan p, int dir, int vi, Tables** out) {
   std::map<int, Tables>& m = dir == 0 ? p->fwd_f32 : dir == 1 ? p->fwd_u8 : p->adj_f32;
-  const bool have = m.count(vi) != 0;
-  const dedisp_status st = build_tables(p, dir, vi, out, nullptr, 0);
-  if (st != DEDISP_OK || have) return st;
-  const hipError_t e = hipStreamSynchronize(nullptr);  // complete for every stream
-  return e == hipSuccess ? DEDISP_OK : hip_fail(e, "building tile tables");
+  auto it = m.find(vi);
+  if (it == m.end()) {
+    const std::vector<Variant>& vs = dir == 1 ? variants_u8() : variants_f32();
+    if (vi < 0 || vi >= (int)vs.size()) return fail(DEDISP_E_INVALID, "variant index out of range");
+    dedisp_status st = check_fits(p, dir, {vi});
+    if (st != DEDISP_OK) return st;
+    static const char* const why[] = {"", "delay span within a wave exceeds the register window",
+                                      "delay span within a block exceeds the LDS row",
+                                      "delay span exceeds the 16-bit offset range",
+                                      "more than 256 input rows overflow its packed sums"};
+    if (p->fits[dir][vi]) return fail(DEDISP_E_UNTUNED, std::string(vs[vi].name) + ": " + why[p->fits[dir][vi]]);
+    st = build_tables(p, dir, {vi});
+    if (st != DEDISP_OK) return st;
+    it = m.find(vi);
+  }
+  if (out) *out = &it->second;
+  return DEDISP_OK;
 }
 
 // Variant preference when nothing was tuned, fastest first as measured on
@@ -273,35 +276,30 @@ static void ensure_chosen(dedisp_plan p, int dir) {
   // the first of the preference order that fits (else the direct kernel), and
   // what the choice by size may take beside it
   const std::vector<int>& order = default_order(dir);
-  std::vector<int> ask(order.begin(), order.begin() + std::min<size_t>(4, order.size()));
+  const size_t top = std::min<size_t>(4, order.size());
+  std::vector<int> ask(order.begin(), order.begin() + top);
   for (const SizeCost& c : size_costs(dir)) ask.push_back(c.vi);
-  (void)check_fits(p, dir, ask);
-  auto fits = [&](int vi) { return check_fits(p, dir, {vi}) == DEDISP_OK && p->fits[dir][vi] == 0; };
-  const std::vector<Variant>& vs = dir == 1 ? variants_u8() : variants_f32();
   int first = -1;
-  for (int vi : order)
-    if (fits(vi)) {
-      first = vi;
-      break;
-    }
-  std::vector<int> build;
-  if (first >= 0) build.push_back(first);
-  for (const SizeCost& c : size_costs(dir))
-    if (first >= 0 && c.vi != first && fits(c.vi)) build.push_back(c.vi);
-  size_t total = 0, at = 0;
-  for (int vi : build) total += table_sizes(p, dir, vs[vi]).total();
-  std::shared_ptr<void> mem;  // one allocation for all of them
-  if (total && shared_malloc(mem, total * sizeof(int32_t)) != hipSuccess) build.resize(1);
+  for (size_t n : {top, order.size()}) {  // the rest is checked only if none of those fits
+    if (first >= 0 || check_fits(p, dir, n == top ? ask : order) != DEDISP_OK) break;
+    for (size_t k = 0; k < n && first < 0; ++k)
+      if (p->fits[dir][order[k]] == 0) first = order[k];
+  }
   p->by_size[dir] = true;
   p->fine[dir].clear();
-  for (int vi : build) {
-    const dedisp_status st = build_tables(p, dir, vi, nullptr, mem, at);
-    if (mem) at += table_sizes(p, dir, vs[vi]).total();
-    if (st != DEDISP_OK && vi == first) first = -1;
-    if (st == DEDISP_OK && vi != first) p->fine[dir].push_back(vi);
-  }
-  (void)hipStreamSynchronize(nullptr);  // the tables are complete for every stream
   v = first;
+  if (first < 0) return;
+  std::vector<int> build = {first};
+  for (const SizeCost& c : size_costs(dir))
+    if (c.vi != first && p->fits[dir][c.vi] == 0) build.push_back(c.vi);
+  std::map<int, Tables>& m = dir == 0 ? p->fwd_f32 : dir == 1 ? p->fwd_u8 : p->adj_f32;
+  build.erase(std::remove_if(build.begin(), build.end(), [&](int vi) { return m.count(vi) != 0; }), build.end());
+  if (build.empty() || build_tables(p, dir, build) == DEDISP_OK) {
+    for (const SizeCost& c : size_costs(dir))
+      if (c.vi != first && m.count(c.vi)) p->fine[dir].push_back(c.vi);
+  } else if (ensure_tables(p, dir, first, nullptr) != DEDISP_OK) {
+    v = -1;
+  }
 }
 
 // Scratch of the allocation-free adjoint (dedisp_adjoint_noalloc): the

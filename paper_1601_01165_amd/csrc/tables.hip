@@ -1,5 +1,5 @@
 // Tile tables built on the GPU from the plan's delay matrix (what they hold is
-// described with struct Tables): one thread per (block row tile, input row).
+// described with struct Tables), those of several variants in one launch.
 #include <algorithm>
 
 #include "internal.h"
@@ -20,19 +20,23 @@ struct DelayView {
   }
 };
 
-// The tables' entries of input row c for row tile rt (not written when blk is
-// null); returns why they do not fit the variant, or 0.
-__device__ int table_column(const Variant& v, const DelayView& delay, int rows_out, int rows_in, int rt, int c,
-                            int32_t* blk, int32_t* wav) {
+// A block of 256 threads takes 64 input rows (c, one per lane) of row tile rt, each wave
+// of it a fourth of the tile's waves: a thread's loads of the delay matrix are what a
+// build waits for.
+constexpr int kCols = 64, kSlices = 4;
+struct Column {
+  int dmin[kSlices][kCols], need[kSlices][kCols];
+};
+
+// The wave entries of this thread's waves; returns why they do not fit the variant, or
+// 0, and what the waves need staged.
+__device__ int table_waves(const Variant& v, const DelayView& delay, int rows_out, int rows_in, int rt, int c, int sbase,
+                           int32_t* wav, int& need) {
   const int DT = v.nwave * v.dpw, WI = v.wav_ints();
   // rows past the end repeat the last row (their results are not stored)
   auto d = [&](int k) { return delay(min(rt * DT + k, rows_out - 1), c); };
-  int dmin = d(0);
-  for (int k = 1; k < DT; ++k) dmin = min(dmin, d(k));
-  const int sbase = v.kind == KIND_TILE_U8 ? dmin & ~15 : dmin & ~3;
-  int need = 0;
-  for (int w = 0; w < v.nwave; ++w) {
-    int32_t* e = blk ? wav + (((size_t)rt * v.nwave + w) * rows_in + c) * WI : nullptr;
+  for (int w = threadIdx.x / kCols; w < v.nwave; w += kSlices) {
+    int32_t* e = wav ? wav + (((size_t)rt * v.nwave + w) * rows_in + c) * WI : nullptr;
     if (v.kind == KIND_WIN_F32) {
       int wmin = d(w * v.dpw);
       for (int j = 1; j < v.dpw; ++j) wmin = min(wmin, d(w * v.dpw + j));
@@ -127,22 +131,50 @@ __device__ int table_column(const Variant& v, const DelayView& delay, int rows_o
         for (int j = v.dpw; j < WI; ++j) e[j] = 0;
     }
   }
-  const int unit = v.kind == KIND_TILE_U8 ? 16 : 4;
-  need = (need + unit - 1) / unit * unit;
-  if (need > v.rowcap) return kTablesRow;
-  if (blk) {
-    blk[((size_t)rt * rows_in + c) * 2 + 0] = sbase;
-    blk[((size_t)rt * rows_in + c) * 2 + 1] = need;
-  }
   return 0;
 }
 
-__global__ __launch_bounds__(256) void build_tables_kernel(Variant v, DelayView delay, int rows_out, int rows_in,
-                                                           int32_t* __restrict__ blk, int32_t* __restrict__ wav) {
-  const int ncb = (rows_in + 255) / 256;
+// The tables' entries of input row c for row tile rt (not written when blk and wav are
+// null); returns why they do not fit the variant, or 0.  Every thread of the block calls it.
+__device__ int table_columns(const Variant& v, const DelayView& delay, int rows_out, int rows_in, int rt, int c,
+                             int32_t* blk, int32_t* wav) {
+  __shared__ Column col;
+  const int lane = threadIdx.x % kCols, slice = threadIdx.x / kCols;
+  const bool live = c < rows_in;
+  int dmin = INT32_MAX;
+  if (live)
+    for (int k = slice; k < v.dt(); k += kSlices) dmin = min(dmin, delay(min(rt * v.dt() + k, rows_out - 1), c));
+  col.dmin[slice][lane] = dmin;
+  __syncthreads();
+  for (int s = 0; s < kSlices; ++s) dmin = min(dmin, col.dmin[s][lane]);
+  const int sbase = v.kind == KIND_TILE_U8 ? dmin & ~15 : dmin & ~3;
+  int need = 0;
+  int why = live ? table_waves(v, delay, rows_out, rows_in, rt, c, sbase, wav, need) : 0;
+  col.need[slice][lane] = need;
+  __syncthreads();
+  for (int s = 0; s < kSlices; ++s) need = max(need, col.need[s][lane]);
+  const int unit = v.kind == KIND_TILE_U8 ? 16 : 4;
+  need = (need + unit - 1) / unit * unit;
+  if (need > v.rowcap) why = max(why, (int)kTablesRow);
+  if (blk && live && slice == 0) {
+    blk[((size_t)rt * rows_in + c) * 2 + 0] = sbase;
+    blk[((size_t)rt * rows_in + c) * 2 + 1] = need;
+  }
+  return why;
+}
+
+// One variant per blockIdx.y, each with its own number of row tiles.
+struct BuildList {
+  TableBuild b[kFitBatch];
+};
+__global__ __launch_bounds__(256) void build_tables_kernel(BuildList list, DelayView delay, int rows_out, int rows_in) {
+  const TableBuild& b = list.b[blockIdx.y];
+  const int ncb = (rows_in + kCols - 1) / kCols;
   const int rt = blockIdx.x / ncb;
-  const int c = (blockIdx.x - rt * ncb) * 256 + threadIdx.x;
-  if (c < rows_in) (void)table_column(v, delay, rows_out, rows_in, rt, c, blk, wav);
+  const int c = (blockIdx.x - rt * ncb) * kCols + threadIdx.x % kCols;
+  if (blockIdx.x == 0)
+    for (int k = threadIdx.x; k < b.slack; k += 256) b.wav[b.ent + k] = 0;
+  if (rt * b.v.dt() < rows_out) (void)table_columns(b.v, delay, rows_out, rows_in, rt, c, b.blk, b.wav);
 }
 
 // Whether the variants fit: bad[k] (zero before) becomes the reason if variant k does not.
@@ -152,47 +184,55 @@ struct VariantList {
 __global__ __launch_bounds__(256) void check_fits_kernel(VariantList list, DelayView delay, int rows_out, int rows_in,
                                                          int* bad) {
   const Variant& v = list.v[blockIdx.y];
-  const int ncb = (rows_in + 255) / 256;
+  const int ncb = (rows_in + kCols - 1) / kCols;
   const int rt = blockIdx.x / ncb;
-  const int c = (blockIdx.x - rt * ncb) * 256 + threadIdx.x;
-  if (c >= rows_in || rt * v.dt() >= rows_out) return;
-  const int why = table_column(v, delay, rows_out, rows_in, rt, c, nullptr, nullptr);
+  const int c = (blockIdx.x - rt * ncb) * kCols + threadIdx.x % kCols;
+  if (rt * v.dt() >= rows_out) return;
+  const int why = table_columns(v, delay, rows_out, rows_in, rt, c, nullptr, nullptr);
   if (why) atomicMax(bad + blockIdx.y, why);
 }
 
 // Adjoint: per (row tile, pass) the least start and greatest end of the
 // pass's staged windows.
-__global__ __launch_bounds__(256) void build_span_kernel(const int32_t* __restrict__ blk, int rows_in, int cc, int npass,
-                                                         int32_t* __restrict__ span) {
+__global__ __launch_bounds__(256) void build_span_kernel(BuildList list, int rows_out, int rows_in) {
+  const TableBuild& b = list.b[blockIdx.y];
+  const int cc = b.v.cc, npass = (rows_in + cc - 1) / cc;
   const int nqb = (npass + 255) / 256;
   const int rt = blockIdx.x / nqb;
   const int q = (blockIdx.x - rt * nqb) * 256 + threadIdx.x;
-  if (q >= npass) return;
+  if (rt * b.v.dt() >= rows_out || q >= npass) return;
   int smin = INT32_MAX, emax = INT32_MIN;
   for (int c = q * cc; c < min(rows_in, (q + 1) * cc); ++c) {
-    const int32_t* b = blk + ((size_t)rt * rows_in + c) * 2;
-    smin = min(smin, b[0]);
-    emax = max(emax, b[0] + b[1]);
+    const int32_t* e = b.blk + ((size_t)rt * rows_in + c) * 2;
+    smin = min(smin, e[0]);
+    emax = max(emax, e[0] + e[1]);
   }
-  span[((size_t)rt * npass + q) * 2 + 0] = smin;
-  span[((size_t)rt * npass + q) * 2 + 1] = emax;
+  b.span[((size_t)rt * npass + q) * 2 + 0] = smin;
+  b.span[((size_t)rt * npass + q) * 2 + 1] = emax;
 }
 
 }  // namespace
 
-hipError_t launch_build_tables(const Variant& v, const int32_t* d_delay, int nchan, int ndm, bool adjoint, int pad,
-                               int32_t* blk, int32_t* wav, int32_t* span, hipStream_t s) {
+hipError_t launch_build_tables(const std::vector<TableBuild>& bs, const int32_t* d_delay, int nchan, int ndm,
+                               bool adjoint, int pad, hipStream_t s) {
+  if (bs.empty() || bs.size() > kFitBatch) return hipErrorInvalidValue;
   const int rows_out = adjoint ? nchan : ndm, rows_in = adjoint ? ndm : nchan;
-  const int64_t nrt = (rows_out + v.dt() - 1) / v.dt();
-  const int64_t grid = nrt * ((rows_in + 255) / 256);
+  BuildList list = {};
+  int64_t grid = 0, sgrid = 0;
+  for (size_t k = 0; k < bs.size(); ++k) {
+    const Variant& v = bs[k].v;
+    const int64_t nrt = (rows_out + v.dt() - 1) / v.dt();
+    list.b[k] = bs[k];
+    grid = std::max(grid, nrt * ((rows_in + kCols - 1) / kCols));
+    sgrid = std::max(sgrid, nrt * (((rows_in + v.cc - 1) / v.cc + 255) / 256));
+  }
   if (grid > 0x7fffffff) return hipErrorInvalidConfiguration;
-  hipLaunchKernelGGL(build_tables_kernel, dim3((unsigned)grid), dim3(256), 0, s, v,
-                     DelayView{d_delay, nchan, adjoint, pad}, rows_out, rows_in, blk, wav);
+  hipLaunchKernelGGL(build_tables_kernel, dim3((unsigned)grid, (unsigned)bs.size()), dim3(256), 0, s, list,
+                     DelayView{d_delay, nchan, adjoint, pad}, rows_out, rows_in);
   hipError_t e = hipGetLastError();
-  if (e == hipSuccess && span) {
-    const int npass = (rows_in + v.cc - 1) / v.cc;
-    hipLaunchKernelGGL(build_span_kernel, dim3((unsigned)(nrt * ((npass + 255) / 256))), dim3(256), 0, s, blk, rows_in,
-                       v.cc, npass, span);
+  if (e == hipSuccess && adjoint) {
+    hipLaunchKernelGGL(build_span_kernel, dim3((unsigned)sgrid, (unsigned)bs.size()), dim3(256), 0, s, list, rows_out,
+                       rows_in);
     e = hipGetLastError();
   }
   return e;
@@ -208,7 +248,7 @@ hipError_t launch_check_fits(const std::vector<const Variant*>& vs, const int32_
     list.v[k] = *vs[k];
     nrt = std::max<int64_t>(nrt, (rows_out + vs[k]->dt() - 1) / vs[k]->dt());
   }
-  const int64_t grid = nrt * ((rows_in + 255) / 256);
+  const int64_t grid = nrt * ((rows_in + kCols - 1) / kCols);
   if (grid > 0x7fffffff) return hipErrorInvalidConfiguration;
   hipError_t e = hipMemsetAsync(bad, 0, vs.size() * sizeof(int), s);
   if (e != hipSuccess) return e;
