@@ -265,4 +265,91 @@ __device__ __forceinline__ void det_commit_int(DetRec* rec, const int* key, doub
   }
 }
 
+// Reduction of N values per lane over the wave, all at once: at each step a
+// lane passes half of its values to a partner and combines the other half, so
+// the N results cost about N + N/2 + N/4 + ... exchanges (24 maxima: some 70
+// instructions instead of 24 reductions of 6 steps).  Step by step the partner
+// differs in lane bit 5, 4, 3, 2, 1, 0, and of the values 2 i and 2 i + 1 a lane
+// keeps the one its bit selects; a value without a neighbour is reduced in both.
+// red_index gives the value a lane ends with (in v[0]).
+template <int BIT>
+__device__ __forceinline__ int red_partner(int x) {
+  static_assert(BIT < 4, "bits 5 and 4 exchange by swaps");
+  // row_ror:8, row_half_mirror, quad_perm [2,3,0,1], quad_perm [1,0,3,2]
+  constexpr int CTRL = BIT == 3 ? 0x128 : BIT == 2 ? 0x141 : BIT == 1 ? 0x4E : 0xB1;
+  return __builtin_amdgcn_update_dpp(0, x, CTRL, 0xf, 0xf, false);
+}
+
+// a: the values of lanes whose bit is 0 next to those of their partners; b: of the others
+template <int BIT>
+__device__ __forceinline__ void red_exchange(int& a, int& b) {
+  if constexpr (BIT == 5) {
+    const auto s = __builtin_amdgcn_permlane32_swap(a, b, false, false);
+    a = s[0];
+    b = s[1];
+  } else if constexpr (BIT == 4) {
+    const auto s = __builtin_amdgcn_permlane16_swap(a, b, false, false);
+    a = s[0];
+    b = s[1];
+  } else {
+    const bool up = (threadIdx.x >> BIT) & 1;
+    const int keep = up ? b : a, send = up ? a : b;
+    a = keep;
+    b = red_partner<BIT>(send);
+  }
+}
+
+template <int N, int BIT = 5>
+__device__ __forceinline__ void red_max(int* v) {
+#pragma unroll
+  for (int i = 0; i < (N + 1) / 2; ++i) {
+    int a = v[2 * i], b = v[2 * i + 1 < N ? 2 * i + 1 : 2 * i];
+    red_exchange<BIT>(a, b);
+    v[i] = max(a, b);
+  }
+  if constexpr (BIT > 0) red_max<(N + 1) / 2, BIT - 1>(v);
+}
+
+template <int N, int BIT = 5>
+__device__ __forceinline__ void red_sum(double* v) {
+#pragma unroll
+  for (int i = 0; i < (N + 1) / 2; ++i) {
+    const double x = v[2 * i], y = v[2 * i + 1 < N ? 2 * i + 1 : 2 * i];
+    int al = __double2loint(x), ah = __double2hiint(x), bl = __double2loint(y), bh = __double2hiint(y);
+    red_exchange<BIT>(al, bl);
+    red_exchange<BIT>(ah, bh);
+    v[i] = __hiloint2double(ah, al) + __hiloint2double(bh, bl);
+  }
+  if constexpr (BIT > 0) red_sum<(N + 1) / 2, BIT - 1>(v);
+}
+
+// The value this lane's result belongs to, or -1 where another lane holds it too.
+template <int N, int BIT = 5>
+__device__ __forceinline__ int red_index(int lane) {
+  const int up = (lane >> BIT) & 1;
+  int i = 0;
+  if constexpr (BIT > 0) i = red_index<(N + 1) / 2, BIT - 1>(lane);
+  return i < 0 || 2 * i + up >= N ? -1 : 2 * i + up;
+}
+
+// The records of G rows at once (uint8): key[k * G + j] are the lane's keys of row j
+// made to order the lanes too, (sum << (IB + 6)) + (tile samples - 1 - start),
+// negative: no window; s[j] and s[G + j] its moments.  rec: row 0's record, `step` records
+// between rows, `rows` of them to write.
+template <int L, int IB, int G>
+__device__ __forceinline__ void det_commit_rows(DetRec* rec, int64_t step, int rows, int* key, double* s, int t0) {
+  const int lane = threadIdx.x & 63;
+  red_max<kDetNW * G>(key);
+  red_sum<2 * G>(s);
+  const int vi = red_index<kDetNW * G>(lane);
+  if (vi >= 0 && vi % G < rows) {
+    DetRec* r = rec + vi % G * step;
+    const int kk = key[0];
+    r->val[vi / G] = kk >> (IB + 6);
+    r->pos[vi / G] = kk < 0 ? -1 : t0 + (64 * L - 1) - (kk & (64 * L - 1));
+  }
+  const int si = red_index<2 * G>(lane);
+  if (si >= 0 && si % G < rows) *((si < G ? &rec->s1 : &rec->s2) + si % G * step * (sizeof(DetRec) / 8)) = s[0];
+}
+
 }  // namespace dd
