@@ -170,8 +170,8 @@ __device__ __forceinline__ void det_commit_f32(DetRec* rec, const float* bval, c
   }
 }
 
-// Integer series (uint8 input: exact sums).  v[0 .. L) holds the lane's run
-// scaled by 2^IB (y << IB).  With E(j) the sum of the first j values from the
+// Integer series (uint8 input: exact sums).  v[0 .. L) holds the lane's run.
+// With E(j) the sum of the first j values y << IB from the
 // lane's first start on (its own prefix for j <= L, then E(j) = E(L) + the
 // next lane's E(j - L)), the key
 //   E(i + w) - (E(i) - (L - 1 - i)) = (B_w(i) << IB) + (L - 1 - i)
@@ -186,29 +186,30 @@ __device__ __forceinline__ void det_commit_f32(DetRec* rec, const float* bval, c
 template <int L, int IB, bool MASK>
 __device__ __forceinline__ void det_lane_int(const int* v, bool owned, int lim, bool s2_u32, int* key, double& s1,
                                              double& s2) {
-  int s1i = 0;
   if (s2_u32) {
     // every y < 2^24 and the lane's sum of squares < 2^32 (the host checks)
     uint32_t q = 0;
 #pragma unroll
     for (int i = 0; i < L; ++i) {
-      const uint32_t y = (!MASK || i < lim) ? (uint32_t)(v[i] >> IB) : 0u;
-      s1i += (int)y;
-      q += __umul24(y, y);
+      const uint32_t y = (!MASK || i < lim) ? (uint32_t)v[i] : 0u;
+      // the product of 24-bit values and the sum in one instruction (the compiler takes three for two samples)
+      asm("v_mad_u32_u24 %0, %1, %1, %0" : "+v"(q) : "v"(y));
     }
     s2 = (double)q;
   } else {
     s2 = 0.0;
 #pragma unroll
     for (int i = 0; i < L; ++i) {
-      const int y = (!MASK || i < lim) ? v[i] >> IB : 0;
-      s1i += y;
-      const double yd = (double)y;
+      const double yd = (double)((!MASK || i < lim) ? v[i] : 0);
       s2 = fma(yd, yd, s2);
     }
   }
-  s1 = owned ? (double)s1i : 0.0;
   if (!owned) s2 = 0.0;
+  int s1i = 0;
+  if (MASK) {
+#pragma unroll
+    for (int i = 0; i < L; ++i) s1i += i < lim ? v[i] : 0;
+  }
 #pragma unroll
   for (int k = 0; k < kDetNW; ++k) key[k] = INT32_MIN;
   int E[L + kDetLook];
@@ -217,7 +218,7 @@ __device__ __forceinline__ void det_lane_int(const int* v, bool owned, int lim, 
 #pragma unroll
   for (int j = 0; j < L + kDetLook; ++j) {
     if (j > 0) {
-      const int e = j <= L ? E[j - 1] + v[j - 1] : E[L] + det_next_lane(0, E[j - L]);
+      const int e = j <= L ? E[j - 1] + (v[j - 1] << IB) : E[L] + det_next_lane(0, E[j - L]);
       E[j] = (MASK && j > lim) ? -(1 << 30) : e;
     }
     if (j < L) Q[j] = (!MASK || j < lim) ? E[j] - (L - 1 - j) : (1 << 30);
@@ -227,6 +228,8 @@ __device__ __forceinline__ void det_lane_int(const int* v, bool owned, int lim, 
       if (i >= 0 && i < L) key[k] = max(key[k], E[j] - Q[i]);
     }
   }
+  if (!MASK) s1i = E[L] >> IB;
+  s1 = owned ? (double)s1i : 0.0;
   // starts outside the tile's owned range: no window
 #pragma unroll
   for (int k = 0; k < kDetNW; ++k) key[k] = owned ? key[k] : INT32_MIN;

@@ -45,8 +45,7 @@ __device__ __forceinline__ void u8_store_tile(const TileArgs& a, int wave, int r
 }
 
 // Single-pulse search in place of the store (see detect_dev.h): each wave
-// passes its rows one at a time through its own LDS slot, scaled by 2^IB for
-// the keys, to give every lane L consecutive samples (the 16-byte chunks are
+// passes its rows one at a time through its own LDS slot, to give every lane L consecutive samples (the 16-byte chunks are
 // XOR-swizzled within groups of eight so that both the writes and the reads
 // are free of bank conflicts); the look-ahead comes from the lanes above.
 template <int Q, int DPW, int NWAVE, typename SUMS, typename PLACE>
@@ -63,8 +62,9 @@ __device__ __forceinline__ void u8_search_tile(const TileArgs& a, uint4* lds, in
   const bool owned = pos0 < a.tile_step;
   const int lim = nvalid - pos0;
   // While a window's sum (at most 32 samples) leaves room for its start in 31 bits, the records
-  // of up to four rows are reduced over the lanes together: 0.10 of 0.62 ms went into
-  // six maxima and two sums per row one after the other (32 channels, 2048 DM trials, 200,000 samples).
+  // of up to four rows are reduced over the lanes together: 0.57 against 0.62 ms with
+  // six maxima and two sums per row one after the other (32 channels, 2048 DM trials, 200,000
+  // samples, of which the sums and their way through LDS take 0.38 ms).
   constexpr int G = DPW < 4 ? DPW : 4;
   const int r0 = rt * NWAVE * DPW + wave * DPW;
   const bool together = a.rows_in < (1 << (25 - IB)) / (32 * 255);
@@ -85,7 +85,7 @@ __device__ __forceinline__ void u8_search_tile(const TileArgs& a, uint4* lds, in
         int s4[4];
         sums(jj, q, s4);
         const int m = place(jj, q) >> 2;  // chunk of samples 4m .. 4m + 3
-        slot[m ^ ((m >> 2) & 7)] = make_int4(s4[0] << IB, s4[1] << IB, s4[2] << IB, s4[3] << IB);
+        slot[m ^ ((m >> 2) & 7)] = make_int4(s4[0], s4[1], s4[2], s4[3]);
       }
       __builtin_amdgcn_wave_barrier();
       int v[L];
