@@ -443,7 +443,7 @@ def measure(wl, args, steps, warmup, plain_loop=True):
         variant_name = dd.variant_names(dt)[vi] if vi >= 0 else "direct"
         kernel_name = ("direct_u8_kernel" if dt == "u8" else "direct_f32_kernel") if vi < 0 else \
             (("u8m_kernel" if variant_name.startswith("u8m_") else "u8s_kernel" if variant_name.startswith("u8s_") else "u8_kernel")
-             if dt == "u8" else "win_kernel")
+             if dt == "u8" else "lane_kernel" if variant_name.startswith("lane_") else "win_kernel")
     elif wl in ("detect_apertif", "detect_lofar"):
         # single-pulse search fused into the dedispersion epilogue (boxcar
         # widths 1..32), the unfused path (store, then search) timed beside it

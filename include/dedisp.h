@@ -280,8 +280,9 @@ dedisp_status dedisp_batch_destroy(dedisp_batch batch);
  * search in its epilogue that fits from an order of preference measured on
  * MI355X (see dedisp_detect_variant), and float32 input, or uint8 input that
  * none fits, dedisperses into the workspace and searches the stored rows, some
- * beams at a time (their series take at most 1 GiB, or one beam's).  The
- * forward variant (dedisp_plan_set_variant, dedisp_autotune) only serves the
+ * beams at a time (their series take at most 1 GiB, or one beam's; float32
+ * beams whose own series take more are searched in place if a variant fits).
+ * The forward variant (dedisp_plan_set_variant, dedisp_autotune) only serves the
  * unfused path.  Asynchronous on
  * `stream`; the first call of a plan and dtype may build tile tables
  * (allocates).

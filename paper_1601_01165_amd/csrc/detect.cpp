@@ -32,7 +32,8 @@ static bool det_fits(dedisp_plan p, bool u8, int vi) {
 // (-1: unfused), otherwise the automatic choice.
 //   float32: unfused.  Storing the series and searching them costs about 0.05 ms
 //     on the 1024-channel, 2000-DM beam; the fused forms lose more by their
-//     registers and overlapping tiles (1.10 ms unfused, 1.50 ms the best fused).
+//     registers and overlapping tiles (1.10 ms unfused, 1.27 ms the best fused).  Where
+//     one beam's series alone take more than 1 GiB: fused, if a variant fits.
 //   uint8: the first that fits from a preference list (fastest first on the
 //     32-channel, 2048-DM beam: the int32 series would be 1.64 GB), or with
 //     fewer blocks than CUs the same kernel with half the samples per tile
@@ -49,8 +50,17 @@ static int det_variant(dedisp_plan p, bool u8) {
   return -1;
 }
 
+static constexpr size_t kUnfusedBytes = (size_t)1 << 30;  // of series in the workspace
+
+static size_t beam_bytes(dedisp_plan p, int nsamp) { return (size_t)p->ndm * (((size_t)nsamp + 3) / 4 * 4) * 4; }
+
 static int det_variant_for(dedisp_plan p, bool u8, int nbeam, int nsamp) {
   const int vi = det_variant(p, u8);
+  if (!u8 && p->var_det_f32 < -1 && beam_bytes(p, nsamp) > kUnfusedBytes) {
+    static const int pref_f32[] = {42, 41, 39, 16, 14, 18, 13, 15, 17};
+    for (int k : pref_f32)
+      if (det_fits(p, false, k)) return k;
+  }
   if (!u8 || p->var_det_u8 >= -1 || vi < 0 || vi == kDetSmallTile) return vi;
   const Variant& v = variants_u8()[vi];
   const int64_t blocks = (int64_t)((p->ndm + v.dt() - 1) / v.dt()) * ((nsamp + det_step(v) - 1) / det_step(v)) * nbeam;
@@ -69,8 +79,7 @@ static size_t rows_ws(int64_t nrows, int nsamp) { return (size_t)nrows * rows_ti
 // search.  Beams go through it in groups whose series take at most 1 GiB (one
 // beam at least), so the workspace does not grow with their number.
 static int unfused_beams(dedisp_plan p, int nbeam, int nsamp) {
-  const size_t one = (size_t)p->ndm * round_up(nsamp, 4) * 4;
-  return (int)std::max<size_t>(1, std::min<size_t>(nbeam, ((size_t)1 << 30) / one));
+  return (int)std::max<size_t>(1, std::min<size_t>(nbeam, kUnfusedBytes / beam_bytes(p, nsamp)));
 }
 
 static size_t fallback_ws(dedisp_plan p, int nbeam, int nsamp) {
@@ -89,7 +98,11 @@ size_t dedisp_detect_workspace_bytes(dedisp_plan p, dedisp_dtype in_type, int32_
   if (!p || nbeam < 1 || nsamp < 1 || (in_type != DEDISP_F32 && in_type != DEDISP_U8)) return 0;
   const bool u8 = in_type == DEDISP_U8;
   const int vi = det_variant_for(p, u8, nbeam, nsamp);
-  if (vi < 0) return fallback_ws(p, nbeam, nsamp);
+  if (vi < 0) {
+    // the forward kernels' tables, so that a search with this workspace allocates nothing
+    (void)dedisp_plan_prepare(p, in_type, 0);
+    return fallback_ws(p, nbeam, nsamp);
+  }
   const Variant& v = (u8 ? variants_u8() : variants_f32())[vi];
   const int64_t ntiles = (nsamp + det_step(v) - 1) / det_step(v);
   return (size_t)nbeam * p->ndm * ntiles * sizeof(DetRec);
