@@ -81,28 +81,25 @@ __device__ __forceinline__ void run_max(float* v, float* best) {
   if constexpr (K + 1 < kDetNW) run_max<K + 1>(v, best);
 }
 
-// One wave per row and group of `group` consecutive tiles.
+// Tiles [ta, tb) of a row by one wave: each width's largest sum and the moments
+// (of the whole wave, in every lane).
 template <bool I32>
-__global__ __launch_bounds__(256) void detect_rows_kernel(const void* __restrict__ rows, int64_t stride, int nrows,
-                                                          int nsamp, int ntiles, int group, int ngroups,
-                                                          DetRec* __restrict__ recs) {
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int g = blockIdx.x % ngroups;
-  const int r = (blockIdx.x / ngroups) * 4 + wave;
-  if (r >= nrows) return;  // whole waves; no block barrier follows
+__device__ __forceinline__ void wave_tiles(const void* rows, int64_t row_off, int nsamp, int ta, int tb, float* m,
+                                           double& s1, double& s2) {
+  const int lane = threadIdx.x & 63;
   const bool owned = kRun * lane < kDetRowsStep;
   float best[kDetNW];
 #pragma unroll
   for (int k = 0; k < kDetNW; ++k) best[k] = -INFINITY;
-  double s1 = 0.0, s2 = 0.0;
-  const int t1 = min(ntiles, (g + 1) * group);
+  s1 = 0.0;
+  s2 = 0.0;
   float v[kRun], nv[kRun];
-  load_run<I32>(rows, (int64_t)r * stride, g * group * kDetRowsStep, nsamp, nv);
-  for (int tt = g * group; tt < t1; ++tt) {
+  load_run<I32>(rows, row_off, ta * kDetRowsStep, nsamp, nv);
+  for (int tt = ta; tt < tb; ++tt) {
     const int t0 = tt * kDetRowsStep;
 #pragma unroll
     for (int i = 0; i < kRun; ++i) v[i] = nv[i];
-    if (tt + 1 < t1) load_run<I32>(rows, (int64_t)r * stride, t0 + kDetRowsStep, nsamp, nv);
+    if (tt + 1 < tb) load_run<I32>(rows, row_off, t0 + kDetRowsStep, nsamp, nv);
     if (owned) {
       const int lim = nsamp - t0 - kRun * lane;  // the lane's starts that hold samples
       if (lim >= kRun) {
@@ -124,11 +121,24 @@ __global__ __launch_bounds__(256) void detect_rows_kernel(const void* __restrict
     }
     run_max<0>(v, best);
   }
-  float m[kDetNW];
 #pragma unroll
   for (int k = 0; k < kDetNW; ++k) m[k] = det_wave_maxf(owned ? best[k] : -INFINITY);
   s1 = det_wave_sum(s1);
   s2 = det_wave_sum(s2);
+}
+
+// One wave per row and group of `group` consecutive tiles.
+template <bool I32>
+__global__ __launch_bounds__(256) void detect_rows_kernel(const void* __restrict__ rows, int64_t stride, int nrows,
+                                                          int nsamp, int ntiles, int group, int ngroups,
+                                                          DetRec* __restrict__ recs) {
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int g = blockIdx.x % ngroups;
+  const int r = (blockIdx.x / ngroups) * 4 + wave;
+  if (r >= nrows) return;  // whole waves; no block barrier follows
+  float m[kDetNW];
+  double s1, s2;
+  wave_tiles<I32>(rows, (int64_t)r * stride, nsamp, g * group, min(ntiles, (g + 1) * group), m, s1, s2);
   if (lane == 0) {
     int4* o = reinterpret_cast<int4*>(recs + (int64_t)r * ngroups + g);
     o[0] = make_int4(__float_as_int(m[0]), __float_as_int(m[1]), __float_as_int(m[2]), __float_as_int(m[3]));
@@ -260,6 +270,92 @@ __global__ __launch_bounds__(256) void det_finish_rows_kernel(const DetRec* __re
   if (stdv) stdv[r] = sd;
 }
 
+// The whole search of a row by one block, its waves taking consecutive shares of
+// the tiles: no records, and no second launch whose few microseconds of latency
+// (loading records, scoring, loading the tiles again) nothing hides.  Bound by the read of
+// the rows: 2,000 rows of 20,000 samples in 33.7 us (4.7 TB/s) against 39.7 in two launches
+// (28 + 9), 818 rows of 9,090 in 23.5 against 27.  Longer rows keep the two launches, whose
+// waves take shorter shares (300 rows of 100,000: 27 us, 42 in blocks of sixteen waves).
+template <bool I32, int NW>
+__global__ __launch_bounds__(64 * NW) void search_row_kernel(const void* __restrict__ rows, int64_t stride, int nsamp,
+                                                             int ntiles, int nwidth, double* __restrict__ snr,
+                                                             int32_t* __restrict__ width, int32_t* __restrict__ start,
+                                                             double* __restrict__ mean, double* __restrict__ stdv) {
+  __shared__ float wm[NW][kDetNW];
+  __shared__ double ws[NW][2];
+  __shared__ int found[NW];
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int r = blockIdx.x;
+  const int64_t row_off = (int64_t)r * stride;
+  const int share = (ntiles + NW - 1) / NW;
+  float m[kDetNW];
+  double s1 = 0.0, s2 = 0.0;
+#pragma unroll
+  for (int k = 0; k < kDetNW; ++k) m[k] = -INFINITY;
+  if (wave * share < ntiles)
+    wave_tiles<I32>(rows, row_off, nsamp, wave * share, min(ntiles, (wave + 1) * share), m, s1, s2);
+  if (lane == 0) {
+#pragma unroll
+    for (int k = 0; k < kDetNW; ++k) wm[wave][k] = m[k];
+    ws[wave][0] = s1;
+    ws[wave][1] = s2;
+  }
+  __syncthreads();
+  // every wave merges and scores, so that all know where to look
+  s1 = ws[0][0];
+  s2 = ws[0][1];
+#pragma unroll
+  for (int w = 1; w < NW; ++w) {
+    s1 += ws[w][0];
+    s2 += ws[w][1];
+  }
+  double md[kDetNW];
+  bool valid[kDetNW];
+  int first[kDetNW];
+#pragma unroll
+  for (int k = 0; k < kDetNW; ++k) {
+    float top = -INFINITY;
+    first[k] = 0;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+      const float f = wm[w][k];
+      first[k] = f > top ? w : first[k];
+      top = f > top ? f : top;
+    }
+    valid[k] = top > -INFINITY;
+    md[k] = (double)top;
+  }
+  double best, mu, sd;
+  const int kb = __builtin_amdgcn_readfirstlane(det_score(s1, s2, nsamp, nwidth, md, valid, best, mu, sd));
+  if (kb >= 0) {
+    float top = (float)md[0];
+    int w0 = first[0];
+#pragma unroll
+    for (int k = 1; k < kDetNW; ++k)
+      if (k == kb) {
+        top = (float)md[k];
+        w0 = first[k];
+      }
+    w0 = __builtin_amdgcn_readfirstlane(w0);
+    int at = -1;
+    const int tb = min(ntiles, (w0 + 1) * share);
+    for (int tt = w0 * share + wave; tt < tb && at < 0; tt += NW)
+      at = find_first<I32>(rows, row_off, nsamp, tt, tt + 1, kb, top);
+    if (lane == 0) found[wave] = at;
+  }
+  __syncthreads();
+  if (threadIdx.x != 0) return;
+  int at = -1;
+  if (kb >= 0)
+    for (int w = 0; w < NW; ++w)
+      if (found[w] >= 0 && (at < 0 || found[w] < at)) at = found[w];
+  snr[r] = best;
+  width[r] = kb < 0 ? -1 : 1 << kb;
+  start[r] = at;
+  if (mean) mean[r] = mu;
+  if (stdv) stdv[r] = sd;
+}
+
 // One wave per series: lane k takes tiles k, k + 64, ... in order (keeping
 // the first of equal sums), then the lanes merge (largest sum, then smallest
 // start), the moments are summed in a fixed order, and lane 0 scores the
@@ -347,6 +443,18 @@ hipError_t launch_detect_rows(const void* rows, bool i32, int64_t stride, int nr
                               DetRec* recs, double* snr, int32_t* width, int32_t* start, double* mean, double* stdv,
                               hipStream_t s) {
   if (nrows < 1 || ntiles < 1) return hipErrorInvalidConfiguration;
+  // A block per row while a wave's share is a few tiles: four waves, or sixteen with rows
+  // too few to fill the chip.
+  if (ntiles <= (nrows < 256 ? 128 : 32)) {
+    auto launch = [&](auto kernel, int nw) {
+      hipLaunchKernelGGL(kernel, dim3((unsigned)nrows), dim3(64 * nw), 0, s, rows, stride, nsamp, ntiles, nwidth, snr,
+                         width, start, mean, stdv);
+      return hipGetLastError();
+    };
+    if (nrows >= 256)
+      return i32 ? launch(search_row_kernel<true, 4>, 4) : launch(search_row_kernel<false, 4>, 4);
+    return i32 ? launch(search_row_kernel<true, 16>, 16) : launch(search_row_kernel<false, 16>, 16);
+  }
   const int group = rows_group(nrows, ntiles), ngroups = (ntiles + group - 1) / group;
   const int64_t nblk = (int64_t)ngroups * ((nrows + 3) / 4);
   if (nblk > 0x7fffffff) return hipErrorInvalidConfiguration;

@@ -1,5 +1,6 @@
 """The search over stored rows against the oracle: row lengths around the tile
-edges and row counts that give a wave one tile or several.  The data are small
+edges, row counts that give a wave one tile or several, and both sides of the line
+between one block per row and records merged by a second kernel.  The data are small
 integers, so every window sum is exact and ties are common: widths, first starts
 and S/N must match (S/N, mean and std to 1e-10: one-pass FP64 moments)."""
 import numpy as np
@@ -12,7 +13,8 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("nrows,ns", [(1, 1), (5, 31), (7, 991), (7, 992), (7, 993), (9, 1024), (3, 2977),
-                                      (6000, 2977), (5500, 1985)])
+                                      (6000, 2977), (5500, 1985), (255, 31744), (255, 31745), (256, 31744),
+                                      (256, 31745), (3, 126976), (3, 126977)])
 @pytest.mark.parametrize("dtype", ["f32", "i32"])
 def test_rows_groups_and_ties(nrows, ns, dtype):
     import paper_1601_01165_amd as dd
