@@ -274,14 +274,16 @@ dedisp_status dedisp_batch_destroy(dedisp_batch batch);
  *   d_snr    [nbeam][ndm] double        d_width [nbeam][ndm] int32
  *   d_start  [nbeam][ndm] int32         d_mean, d_std [nbeam][ndm] double, or NULL
  *   d_workspace: device scratch of at least dedisp_detect_workspace_bytes(...)
- *            bytes, 16-byte aligned (contents on return: undefined).
+ *            bytes for this call or for one with no fewer beams and samples,
+ *            16-byte aligned (contents on return: undefined).
  * Uses the path set with dedisp_plan_set_detect_variant or kept by
  * dedisp_detect_autotune; else uint8 input takes the first variant with the
  * search in its epilogue that fits from an order of preference measured on
  * MI355X (see dedisp_detect_variant), and float32 input, or uint8 input that
  * none fits, dedisperses into the workspace and searches the stored rows, some
- * beams at a time (their series take at most 1 GiB, or one beam's; float32
- * beams whose own series take more are searched in place if a variant fits).
+ * beams at a time: their series and records take at most 1 GiB, or one beam's,
+ * and no more than the workspace has room for.  float32 beams that alone take
+ * more than either are searched in place if a variant fits.
  * The forward variant (dedisp_plan_set_variant, dedisp_autotune) only serves the
  * unfused path.  Asynchronous on
  * `stream`; the first call of a plan and dtype may build tile tables
@@ -293,8 +295,9 @@ dedisp_status dedisp_detect(dedisp_plan plan, int32_t nbeam, int32_t nsamp, cons
                             int32_t* d_start, double* d_mean, double* d_std, void* d_workspace,
                             size_t workspace_bytes, void* stream);
 
-/* Workspace bytes dedisp_detect needs for these sizes with the variant it
- * would use now (0 for invalid arguments).  May build tile tables. */
+/* Workspace bytes with which dedisp_detect runs a call of these sizes, and every
+ * one with no more beams and no more samples, on the path set or chosen now
+ * (0 for invalid arguments).  May build tile tables. */
 size_t dedisp_detect_workspace_bytes(dedisp_plan plan, dedisp_dtype in_type, int32_t nbeam, int32_t nsamp);
 
 /* The variant dedisp_detect would use for in_type (an index of

@@ -326,13 +326,18 @@ def detect(x: torch.Tensor, plan: Plan, nsamp: int | None = None, w: torch.Tenso
         if w.numel() != nc or not w.is_cuda:
             raise ValueError("weights must be a float32 GPU tensor of nchan values")
     L = lib()
-    nbytes = L.dedisp_detect_workspace_bytes(plan.handle, dt, nb, nsamp)
-    if workspace is None or workspace.numel() * workspace.element_size() < nbytes:
-        workspace = torch.empty(max(nbytes, 16), dtype=torch.uint8, device=xr.device)
     o = _det_outputs((nb, plan.ndm), xr.device)
-    check(L.dedisp_detect(plan.handle, nb, nsamp, _ptr(xr), dt, xr.stride(1), _ptr(w), nwidth, _ptr(o["snr"]),
-                          _ptr(o["width"]), _ptr(o["start"]), _ptr(o["mean"]), _ptr(o["std"]), _ptr(workspace),
-                          workspace.numel() * workspace.element_size(), _stream(xr.device)), "detect")
+
+    def call(ws):
+        return L.dedisp_detect(plan.handle, nb, nsamp, _ptr(xr), dt, xr.stride(1), _ptr(w), nwidth, _ptr(o["snr"]),
+                               _ptr(o["width"]), _ptr(o["start"]), _ptr(o["mean"]), _ptr(o["std"]), _ptr(ws),
+                               ws.numel() * ws.element_size(), _stream(xr.device))
+
+    status = _clib.E_WORKSPACE if workspace is None else call(workspace)
+    if status == _clib.E_WORKSPACE:
+        nbytes = L.dedisp_detect_workspace_bytes(plan.handle, dt, nb, nsamp)
+        status = call(torch.empty(max(nbytes, 16), dtype=torch.uint8, device=xr.device))
+    check(status, "detect")
     return {k: v[0] for k, v in o.items()} if squeeze else o
 
 

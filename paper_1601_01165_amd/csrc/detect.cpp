@@ -50,42 +50,95 @@ static int det_variant(dedisp_plan p, bool u8) {
   return -1;
 }
 
-static constexpr size_t kUnfusedBytes = (size_t)1 << 30;  // of series in the workspace
-
-static size_t beam_bytes(dedisp_plan p, int nsamp) { return (size_t)p->ndm * (((size_t)nsamp + 3) / 4 * 4) * 4; }
-
-static int det_variant_for(dedisp_plan p, bool u8, int nbeam, int nsamp) {
-  const int vi = det_variant(p, u8);
-  if (!u8 && p->var_det_f32 < -1 && beam_bytes(p, nsamp) > kUnfusedBytes) {
-    static const int pref_f32[] = {42, 41, 39, 16, 14, 18, 13, 15, 17};
-    for (int k : pref_f32)
-      if (det_fits(p, false, k)) return k;
-  }
-  if (!u8 || p->var_det_u8 >= -1 || vi < 0 || vi == kDetSmallTile) return vi;
-  const Variant& v = variants_u8()[vi];
-  const int64_t blocks = (int64_t)((p->ndm + v.dt() - 1) / v.dt()) * ((nsamp + det_step(v) - 1) / det_step(v)) * nbeam;
-  // looked at on the first call whatever its size, so that later ones allocate nothing
-  const bool small = det_fits(p, true, kDetSmallTile);
-  return small && blocks < p->ncu ? kDetSmallTile : vi;
-}
-
 static size_t round_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
 static int64_t rows_tiles(int nsamp) { return (nsamp + kDetRowsStep - 1) / kDetRowsStep; }
 
 static size_t rows_ws(int64_t nrows, int nsamp) { return (size_t)nrows * rows_tiles(nsamp) * sizeof(DetRec); }
 
-// Unfused path: the forward map of some beams into the workspace, then the row
-// search.  Beams go through it in groups whose series take at most 1 GiB (one
-// beam at least), so the workspace does not grow with their number.
-static int unfused_beams(dedisp_plan p, int nbeam, int nsamp) {
-  return (int)std::max<size_t>(1, std::min<size_t>(nbeam, kUnfusedBytes / beam_bytes(p, nsamp)));
+// Records of a fused search.
+static size_t fused_ws(dedisp_plan p, const Variant& v, int nbeam, int nsamp) {
+  return (size_t)nbeam * p->ndm * ((nsamp + det_step(v) - 1) / det_step(v)) * sizeof(DetRec);
 }
 
-static size_t fallback_ws(dedisp_plan p, int nbeam, int nsamp) {
-  const int64_t nrows = (int64_t)unfused_beams(p, nbeam, nsamp) * p->ndm;
-  const size_t rows = round_up((size_t)nrows * round_up(nsamp, 4) * 4, 256);
-  return rows + rows_ws(nrows, nsamp);
+// Unfused path: the forward map of some beams into the workspace, then the row
+// search.  Beams go through it in groups whose series and records take at most
+// 1 GiB (one beam at least), fewer at a time in a smaller workspace.
+static constexpr size_t kUnfusedBytes = (size_t)1 << 30;
+static constexpr size_t kUnfusedSlack = 256;  // the records start on the next multiple of this
+
+static size_t unfused_beam_ws(dedisp_plan p, int nsamp) {
+  return (size_t)p->ndm * (round_up(nsamp, 4) * 4 + rows_tiles(nsamp) * sizeof(DetRec));
+}
+
+static size_t unfused_ws(dedisp_plan p, int nbeam, int nsamp) {
+  const size_t beam = unfused_beam_ws(p, nsamp);
+  return std::min(nbeam * beam, std::max(kUnfusedBytes, beam)) + kUnfusedSlack;
+}
+
+// Beams per group in a workspace of ws_bytes; 0: not even one fits.
+static int unfused_beams(dedisp_plan p, int nbeam, int nsamp, size_t ws_bytes) {
+  const size_t beam = unfused_beam_ws(p, nsamp);
+  if (ws_bytes < kUnfusedSlack + beam) return 0;
+  const size_t most = std::max<size_t>(1, kUnfusedBytes / beam);
+  return (int)std::min({(size_t)nbeam, most, (ws_bytes - kUnfusedSlack) / beam});
+}
+
+// The variant that searches float32 beams in place where their series are too
+// large for the workspace, or -1.
+static int f32_in_place(dedisp_plan p) {
+  static const int pref_f32[] = {42, 41, 39, 16, 14, 18, 13, 15, 17};
+  for (int k : pref_f32)
+    if (det_fits(p, false, k)) return k;
+  return -1;
+}
+
+// uint8: the small tile beside the default variant vi, or -1.  Looked at on the
+// first call whatever its size, so that later ones allocate nothing.
+static int u8_small_tile(dedisp_plan p, int vi) {
+  return vi >= 0 && vi != kDetSmallTile && p->var_det_u8 < -1 && det_fits(p, true, kDetSmallTile) ? kDetSmallTile : -1;
+}
+
+// The path of a call with a workspace of ws_bytes: a fused variant, or -1 and the
+// beams per group.  False if the workspace serves none.  A workspace sized
+// (search_ws) for a call serves every call with no more beams and no more samples.
+static bool search_path(dedisp_plan p, bool u8, int nbeam, int nsamp, size_t ws_bytes, int& vi, int& beams) {
+  const std::vector<Variant>& vs = u8 ? variants_u8() : variants_f32();
+  vi = det_variant(p, u8);
+  beams = 0;
+  if (u8) {
+    const int small = u8_small_tile(p, vi);
+    if (small >= 0) {
+      const Variant& v = vs[vi];
+      const int64_t blocks = (int64_t)((p->ndm + v.dt() - 1) / v.dt()) * ((nsamp + det_step(v) - 1) / det_step(v)) * nbeam;
+      if (blocks < p->ncu && ws_bytes >= fused_ws(p, vs[small], nbeam, nsamp)) vi = small;
+    }
+  } else if (vi < 0 && p->var_det_f32 < -1) {
+    // beams larger than a group, or than the workspace (sized for such): in place
+    if (unfused_beam_ws(p, nsamp) > std::min(kUnfusedBytes, ws_bytes - std::min(ws_bytes, kUnfusedSlack)))
+      vi = f32_in_place(p);
+  }
+  if (vi >= 0) return ws_bytes >= fused_ws(p, vs[vi], nbeam, nsamp);
+  beams = unfused_beams(p, nbeam, nsamp, ws_bytes);
+  return beams > 0;
+}
+
+static size_t search_ws(dedisp_plan p, bool u8, int nbeam, int nsamp) {
+  const std::vector<Variant>& vs = u8 ? variants_u8() : variants_f32();
+  int vi = det_variant(p, u8);
+  if (!u8 && vi < 0 && p->var_det_f32 < -1 && unfused_beam_ws(p, nsamp) > kUnfusedBytes) vi = f32_in_place(p);
+  if (vi < 0) return unfused_ws(p, nbeam, nsamp);
+  size_t n = fused_ws(p, vs[vi], nbeam, nsamp);
+  const int small = u8 ? u8_small_tile(p, vi) : -1;
+  if (small >= 0) {
+    // The small tile's records too, as far as a call with fewer blocks than CUs can need
+    // them: row tiles x time tiles x beams < CUs, each time tile cut into `cut`.
+    const Variant& v = vs[vi];
+    const int64_t tiles = (p->ncu - 1) / ((p->ndm + v.dt() - 1) / v.dt());
+    const int64_t cut = (det_step(v) + det_step(vs[small]) - 1) / det_step(vs[small]);
+    n = std::max(n, std::min(fused_ws(p, vs[small], nbeam, nsamp), (size_t)(tiles * cut) * p->ndm * sizeof(DetRec)));
+  }
+  return n;
 }
 
 }  // namespace dd
@@ -97,15 +150,10 @@ extern "C" {
 size_t dedisp_detect_workspace_bytes(dedisp_plan p, dedisp_dtype in_type, int32_t nbeam, int32_t nsamp) {
   if (!p || nbeam < 1 || nsamp < 1 || (in_type != DEDISP_F32 && in_type != DEDISP_U8)) return 0;
   const bool u8 = in_type == DEDISP_U8;
-  const int vi = det_variant_for(p, u8, nbeam, nsamp);
-  if (vi < 0) {
-    // the forward kernels' tables, so that a search with this workspace allocates nothing
-    (void)dedisp_plan_prepare(p, in_type, 0);
-    return fallback_ws(p, nbeam, nsamp);
-  }
-  const Variant& v = (u8 ? variants_u8() : variants_f32())[vi];
-  const int64_t ntiles = (nsamp + det_step(v) - 1) / det_step(v);
-  return (size_t)nbeam * p->ndm * ntiles * sizeof(DetRec);
+  const size_t n = search_ws(p, u8, nbeam, nsamp);
+  // the forward kernels' tables, so that a search with this workspace allocates nothing
+  if (det_variant(p, u8) < 0) (void)dedisp_plan_prepare(p, in_type, 0);
+  return n;
 }
 
 int32_t dedisp_detect_variant(dedisp_plan p, dedisp_dtype in_type) {
@@ -140,22 +188,20 @@ dedisp_status dedisp_detect(dedisp_plan p, int32_t nbeam, int32_t nsamp, const v
   if (((uintptr_t)d_in & 15u) || (in_stride * esz) % 16 || (d_w && ((uintptr_t)d_w & 3)))
     return fail(DEDISP_E_ALIGN, "pointers and row byte sizes must be multiples of 16 bytes");
   if (!d_ws) return fail(DEDISP_E_WORKSPACE, "workspace is NULL");
+  int vi, beams;
+  if (!search_path(p, u8, nbeam, nsamp, ws_bytes, vi, beams)) return fail(DEDISP_E_WORKSPACE, "workspace too small");
   if ((uintptr_t)d_ws & 15u) return fail(DEDISP_E_ALIGN, "workspace must be 16-byte aligned");
-  if (ws_bytes < dedisp_detect_workspace_bytes(p, in_type, nbeam, nsamp))
-    return fail(DEDISP_E_WORKSPACE, "workspace too small");
   hipStream_t s = (hipStream_t)stream;
   const int64_t nseries = (int64_t)nbeam * p->ndm;
   if (nseries > 0x7ffffff0) return fail(DEDISP_E_SHAPE, "too many series");
-  const int vi = det_variant_for(p, u8, nbeam, nsamp);
   hipError_t e;
   if (vi < 0) {
     const int64_t stride = round_up(nsamp, 4);
-    const int step = unfused_beams(p, nbeam, nsamp);
     void* rows = d_ws;
-    DetRec* recs = (DetRec*)((char*)d_ws + round_up((size_t)step * p->ndm * stride * 4, 256));
+    DetRec* recs = (DetRec*)((char*)d_ws + round_up((size_t)beams * p->ndm * stride * 4, kUnfusedSlack));
     const int ntiles = (int)rows_tiles(nsamp);
-    for (int b = 0; b < nbeam; b += step) {
-      const int nb = std::min(step, nbeam - b);
+    for (int b = 0; b < nbeam; b += beams) {
+      const int nb = std::min(beams, nbeam - b);
       const int64_t s0 = (int64_t)b * p->ndm;
       st = dedisp_execute(p, nb, nsamp, (const char*)d_in + (int64_t)b * p->nchan * in_stride * esz, in_type, in_stride,
                           d_w, rows, u8 ? DEDISP_I32 : DEDISP_F32, stride, stream);
@@ -224,7 +270,7 @@ dedisp_status dedisp_detect_autotune(dedisp_plan p, int32_t nbeam, int32_t nsamp
   const int64_t in_stride = ((int64_t)nsamp + p->max_delay + q - 1) / q * q;
   const int64_t nseries = (int64_t)nbeam * p->ndm;
   // the unfused path needs the most workspace
-  const size_t ws_bytes = fallback_ws(p, nbeam, nsamp);
+  const size_t ws_bytes = unfused_ws(p, nbeam, nsamp);
   void *d_in = nullptr, *d_ws = nullptr, *d_res = nullptr;
   hipError_t e = hipMalloc(&d_in, (size_t)nbeam * p->nchan * in_stride * esz);
   if (e == hipSuccess) e = hipMalloc(&d_ws, ws_bytes);
