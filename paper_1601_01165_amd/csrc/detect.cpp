@@ -269,8 +269,12 @@ dedisp_status dedisp_detect_autotune(dedisp_plan p, int32_t nbeam, int32_t nsamp
   const int64_t q = 16 / esz;
   const int64_t in_stride = ((int64_t)nsamp + p->max_delay + q - 1) / q * q;
   const int64_t nseries = (int64_t)nbeam * p->ndm;
-  // the unfused path needs the most workspace
-  const size_t ws_bytes = unfused_ws(p, nbeam, nsamp);
+  // room for every path: the series of a few beams, or the records of all of them (64
+  // bytes per series and tile: more than 1 GiB from about 30 GiB of series on)
+  size_t ws_bytes = unfused_ws(p, nbeam, nsamp);
+  for (int vi = 0; vi < nv; ++vi)
+    if (det_fits(p, u8, vi))
+      ws_bytes = std::max(ws_bytes, fused_ws(p, (u8 ? variants_u8() : variants_f32())[vi], nbeam, nsamp));
   void *d_in = nullptr, *d_ws = nullptr, *d_res = nullptr;
   hipError_t e = hipMalloc(&d_in, (size_t)nbeam * p->nchan * in_stride * esz);
   if (e == hipSuccess) e = hipMalloc(&d_ws, ws_bytes);

@@ -86,3 +86,19 @@ def test_f32_shorter_calls(nb, long, short):
         _same(dd.detect(x, plan, nsamp=ns, workspace=mine), got)
         assert torch.cuda.max_memory_allocated() - before < 1 << 22
         _same(dd.detect(x, plan, nsamp=ns, workspace=mine[:16]), got)
+
+
+def test_autotune_times_every_fused_variant_of_a_large_call():
+    """512 beams of 1024 DM trials x 16,000 samples: the records of the small tiles take more than
+    the series of one group (1 GiB), and every variant that fits is timed all the same."""
+    dd, plan = _dd(), _plan(2, 1024, 0.05)
+    names, fit = dd.variant_names("u8"), set()
+    for i, name in enumerate(names):
+        try:
+            plan.set_detect_variant(i, "u8")
+            fit.add(name)
+        except dd.DedispError:
+            pass
+    assert len(fit) > 10
+    times = plan.autotune_detect(512, 16000, "u8")
+    assert set(times) == fit | {"unfused"}
