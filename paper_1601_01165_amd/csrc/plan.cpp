@@ -329,21 +329,36 @@ static void* scratch_address(int device) {
   return ptr;
 }
 
-// The adjoint's launches with the partial-sum buffer given (null when no
-// weight gradient is asked for).  With may_allocate false the plan's chosen
-// adjoint variant and its tables must exist already (nothing is built).
-static dedisp_status adjoint_impl(dedisp_plan p, int32_t nbeam, int32_t nsamp, int32_t nin, const float* d_g,
+// FP64 partial sums of the weight gradient with variant vi: one per channel and
+// (beam, time part), 256-sample parts for the direct kernel, the variant's time
+// tiles otherwise.
+static size_t partial_bytes(dedisp_plan p, int vi, int nbeam, int64_t nin) {
+  const int64_t part = vi < 0 ? 256 : variants_f32()[vi].st();
+  return (size_t)nbeam * (size_t)((nin + part - 1) / part) * (size_t)p->nchan * sizeof(double);
+}
+
+// The variant of an adjoint call: the choice by size, except where only the default
+// variant's partial sums fit the fixed scratch (few channels and long rows take
+// short tiles: 8 channels, 36e6 samples need 9.0 MB in tiles of 256 samples and 1.8 MB
+// in those of 1280).  Calls with a workspace choose the same, so that both entry
+// points give the same bits.
+static int pick_adjoint(dedisp_plan p, int nbeam, int64_t nin, bool grad_w) {
+  const int vi = pick_variant(p, 2, nbeam, nin);
+  return grad_w && partial_bytes(p, vi, nbeam, nin) > kNoAllocScratchBytes &&
+                 partial_bytes(p, p->var_adj, nbeam, nin) <= kNoAllocScratchBytes
+             ? p->var_adj
+             : vi;
+}
+
+// The adjoint's launches by variant vi with the partial-sum buffer given (null
+// when no weight gradient is asked for).  With may_allocate false the
+// variant's tables must exist already (nothing is built).
+static dedisp_status adjoint_impl(dedisp_plan p, int vi, int32_t nbeam, int32_t nsamp, int32_t nin, const float* d_g,
                                   int64_t g_stride, const float* d_w, const float* d_in, int64_t in_stride,
                                   float* d_grad_in, int64_t gi_stride, float* d_grad_w, double* partial,
                                   hipStream_t s, bool may_allocate) {
   hipError_t e;
   int nparts;
-  if (may_allocate) {
-    ensure_chosen(p, 2);
-  } else if (p->var_adj == -2) {
-    return fail(DEDISP_E_INVALID, "the adjoint kernel is not chosen yet: call dedisp_plan_prepare first");
-  }
-  const int vi = pick_variant(p, 2, nbeam, nin);
   if (vi < 0) {
     e = launch_direct_adjoint(d_g, g_stride, g_stride * p->ndm, p->d_delay, p->nchan, p->ndm, nsamp, nin, d_w,
                               d_grad_in, gi_stride, gi_stride * p->nchan, d_in, in_stride, in_stride * p->nchan,
@@ -661,17 +676,15 @@ dedisp_status dedisp_adjoint(dedisp_plan p, int32_t nbeam, int32_t nsamp, int32_
     if (ws_bytes < dedisp_adjoint_workspace_bytes(p, nbeam, nin)) return fail(DEDISP_E_WORKSPACE, "workspace too small");
     if ((uintptr_t)d_ws & 7) return fail(DEDISP_E_ALIGN, "workspace must be 8-byte aligned");
   }
-  return adjoint_impl(p, nbeam, nsamp, nin, d_g, g_stride, d_w, d_in, in_stride, d_grad_in, gi_stride, d_grad_w,
-                      d_grad_w ? (double*)d_ws : nullptr, (hipStream_t)stream, true);
+  ensure_chosen(p, 2);
+  return adjoint_impl(p, pick_adjoint(p, nbeam, nin, d_grad_w != nullptr), nbeam, nsamp, nin, d_g, g_stride, d_w, d_in,
+                      in_stride, d_grad_in, gi_stride, d_grad_w, d_grad_w ? (double*)d_ws : nullptr, (hipStream_t)stream,
+                      true);
 }
 
 size_t dedisp_adjoint_noalloc_bytes(dedisp_plan p, int32_t nbeam, int32_t nin) {
   if (!p || nbeam < 1 || nin < 1 || p->var_adj == -2) return 0;
-  const int vi = pick_variant(p, 2, nbeam, nin);
-  // one FP64 partial sum per channel and (beam, time part): 256-sample parts
-  // for the direct kernel, the variant's time tiles otherwise
-  const int64_t part = vi < 0 ? 256 : variants_f32()[vi].st();
-  return (size_t)nbeam * (size_t)((nin + part - 1) / part) * (size_t)p->nchan * sizeof(double);
+  return partial_bytes(p, pick_adjoint(p, nbeam, nin, true), nbeam, nin);
 }
 
 dedisp_status dedisp_adjoint_noalloc(dedisp_plan p, int32_t nbeam, int32_t nsamp, int32_t nin, const float* d_g,
@@ -697,8 +710,8 @@ dedisp_status dedisp_adjoint_noalloc(dedisp_plan p, int32_t nbeam, int32_t nsamp
     partial = static_cast<double*>(scratch_address(dev));
     if (!partial) return DEDISP_E_HIP;
   }
-  return adjoint_impl(p, nbeam, nsamp, nin, d_g, g_stride, d_w, d_in, in_stride, d_grad_in, gi_stride, d_grad_w,
-                      partial, (hipStream_t)stream, false);
+  return adjoint_impl(p, pick_adjoint(p, nbeam, nin, d_grad_w != nullptr), nbeam, nsamp, nin, d_g, g_stride, d_w, d_in,
+                      in_stride, d_grad_in, gi_stride, d_grad_w, partial, (hipStream_t)stream, false);
 }
 
 }  // extern "C"
