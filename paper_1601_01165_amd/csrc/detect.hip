@@ -274,8 +274,8 @@ __global__ __launch_bounds__(256) void det_finish_rows_kernel(const DetRec* __re
 // the tiles: no records, and no second launch whose few microseconds of latency
 // (loading records, scoring, loading the tiles again) nothing hides.  Bound by the read of
 // the rows: 2,000 rows of 20,000 samples in 33.7 us (4.7 TB/s) against 39.7 in two launches
-// (28 + 9), 818 rows of 9,090 in 23.5 against 27.  Longer rows keep the two launches, whose
-// waves take shorter shares (300 rows of 100,000: 27 us, 42 in blocks of sixteen waves).
+// (28 + 9), 818 rows of 9,090 in 23.5 against 27.  launch_detect_rows says which rows
+// take it.
 template <bool I32, int NW>
 __global__ __launch_bounds__(64 * NW) void search_row_kernel(const void* __restrict__ rows, int64_t stride, int nsamp,
                                                              int ntiles, int nwidth, double* __restrict__ snr,
@@ -431,33 +431,42 @@ __global__ __launch_bounds__(256) void det_finish_kernel(const DetRec* __restric
   if (stdv) stdv[sidx] = sd;
 }
 
-// Tiles one wave of the row search takes: enough waves to fill the chip about
-// twice come first (2,000 rows of 20,000 samples: 42,000 tiles in groups of 4);
+// Tiles one wave of the row search's first launch takes: enough waves to fill the
+// chip about twice come first (300 rows of 100,000 samples: 30,300 tiles in groups of 3);
 // longer groups then save wave reductions and records.
 static int rows_group(int nrows, int ntiles) {
   const int64_t tiles = (int64_t)nrows * ntiles;
   return (int)std::max<int64_t>(1, std::min<int64_t>({tiles / 8192, ntiles, 8}));
 }
 
+// Work items of one launch (a 32-bit count).
+static constexpr int64_t kMaxWorkItems = 0xffffffffll;
+
 hipError_t launch_detect_rows(const void* rows, bool i32, int64_t stride, int nrows, int nsamp, int ntiles, int nwidth,
                               DetRec* recs, double* snr, int32_t* width, int32_t* start, double* mean, double* stdv,
                               hipStream_t s) {
   if (nrows < 1 || ntiles < 1) return hipErrorInvalidConfiguration;
-  // A block per row while a wave's share is a few tiles: four waves, or sixteen with rows
-  // too few to fill the chip.
-  if (ntiles <= (nrows < 256 ? 128 : 32)) {
+  // A block of four waves per row while a wave's share of the tiles is short: up to 32
+  // tiles, or 12 where there are fewer rows than would fill the chip (GPU times in us, one
+  // launch against two: 255 rows of 32 tiles 10.5 and 12.3, of 12 tiles 6.6 and 8.5; 64 rows of
+  // 32 tiles 9.9 and 7.8, of 12 tiles 6.5 and 7.4; 300 rows of 101 tiles 42 and 27).  One
+  // wave where four would have no tile each: 100,000 rows of 500 samples 116 us, 314 with four waves; 6,000
+  // rows of 3 tiles level; 50,000 rows of 2 tiles 102 and 180.  Few such rows of 2 or 3 tiles keep four
+  // (64 rows of 3: 5.1 and 6.9).  One wave too where four a row would be 2^32 work items.
+  if (ntiles <= (nrows < 192 ? 12 : 32)) {
     auto launch = [&](auto kernel, int nw) {
+      if ((int64_t)nrows * 64 * nw > kMaxWorkItems) return hipErrorInvalidConfiguration;
       hipLaunchKernelGGL(kernel, dim3((unsigned)nrows), dim3(64 * nw), 0, s, rows, stride, nsamp, ntiles, nwidth, snr,
                          width, start, mean, stdv);
       return hipGetLastError();
     };
-    if (nrows >= 256)
-      return i32 ? launch(search_row_kernel<true, 4>, 4) : launch(search_row_kernel<false, 4>, 4);
-    return i32 ? launch(search_row_kernel<true, 16>, 16) : launch(search_row_kernel<false, 16>, 16);
+    const bool one = ntiles == 1 || (ntiles <= 3 && nrows >= 4096) || (int64_t)nrows * 256 > kMaxWorkItems;
+    if (one) return i32 ? launch(search_row_kernel<true, 1>, 1) : launch(search_row_kernel<false, 1>, 1);
+    return i32 ? launch(search_row_kernel<true, 4>, 4) : launch(search_row_kernel<false, 4>, 4);
   }
   const int group = rows_group(nrows, ntiles), ngroups = (ntiles + group - 1) / group;
   const int64_t nblk = (int64_t)ngroups * ((nrows + 3) / 4);
-  if (nblk > 0x7fffffff) return hipErrorInvalidConfiguration;
+  if (nblk * 256 > kMaxWorkItems) return hipErrorInvalidConfiguration;
   const dim3 grid((unsigned)nblk), fin((unsigned)((nrows + 3) / 4));
   if (i32) {
     hipLaunchKernelGGL((detect_rows_kernel<true>), grid, dim3(256), 0, s, rows, stride, nrows, nsamp, ntiles, group,
