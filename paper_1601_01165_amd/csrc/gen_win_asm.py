@@ -805,22 +805,24 @@ ROW_SHAPES = [
 ]
 
 
-# (TP, DPW, NWIN, CC[, first accumulator VGPR]) combinations with a jump-form pass
+# (TP, DPW, NWIN, CC, first accumulator VGPR, forms of the jump pass that a variant runs:
+# "slots", the same reading the whole window ("full"), or with the next row's window
+# read ahead ("ahead"); none where the variants of the shape run row blocks)
 JMP_VARIANTS = [
-    (20, 4, 44, 4),
-    (20, 8, 56, 4),
-    (20, 8, 56, 6),
-    (28, 4, 48, 4),
-    (12, 4, 36, 4),
-    (20, 4, 40, 3, 8),
-    (20, 4, 40, 6, 8),
-    (20, 4, 40, 8, 8),
-    (20, 4, 40, 10, 8),
-    (20, 4, 44, 8, 4),
-    (20, 4, 44, 10, 4),
-    (20, 4, 84, 8, 4),
-    (20, 4, 84, 3, 4),
-    (12, 4, 32, 8, 8),
+    (20, 4, 44, 4, ACC0, ("ahead", "full")),
+    (20, 8, 56, 4, ACC0, ("slots", "full")),
+    (20, 8, 56, 6, ACC0, ("slots", "full")),
+    (28, 4, 48, 4, ACC0, ("ahead",)),
+    (12, 4, 36, 4, ACC0, ("ahead",)),
+    (20, 4, 40, 3, 8, ()),
+    (20, 4, 40, 6, 8, ()),
+    (20, 4, 40, 8, 8, ("full",)),
+    (20, 4, 40, 10, 8, ()),
+    (20, 4, 44, 8, 4, ()),
+    (20, 4, 44, 10, 4, ()),
+    (20, 4, 84, 8, 4, ("ahead",)),
+    (20, 4, 84, 3, 4, ("ahead",)),
+    (12, 4, 32, 8, 8, ()),
 ]
 
 
@@ -882,8 +884,6 @@ def main(out_path):
         "// table entry's per-row values are block offsets o * JmpBlockBytes<TP>.\n",
         "template <int TP, int DPW, int NWIN, int CC, bool WEIGHTED, bool FULL, int ROWCAP>\n",
         "struct JmpPass;\n",
-        "template <int TP, int DPW, int NWIN, int CC>\n",
-        "struct HasJmpPass : std::false_type {};\n",
         "// The form of 4 DM trials per wave that reads the next row's window while the\n",
         "// last slot adds: ea and eb hold the next two rows' entries, toff the third's.\n",
         "template <int TP, int DPW, int NWIN, int CC, int ROWCAP>\n",
@@ -892,22 +892,16 @@ def main(out_path):
         "template <int TP, int DPW, int NWIN, int CC>\n",
         "struct JmpAcc0 { static constexpr int value = 0; };\n",
     ]
-    for jv in JMP_VARIANTS:
-        tp, dpw, nwin, cc = jv[:4]
-        acc0 = jv[4] if len(jv) > 4 else ACC0
+    for tp, dpw, nwin, cc, acc0, forms in JMP_VARIANTS:
         assert jmp_block_bytes(tp) == 4 * tp + 4
-        parts.append(f"template <> struct HasJmpPass<{tp}, {dpw}, {nwin}, {cc}> : std::true_type {{}};\n")
         parts.append(f"template <> struct JmpAcc0<{tp}, {dpw}, {nwin}, {cc}> {{ static constexpr int value = {acc0}; }};\n")
     parts.append("\n")
-    for jv in JMP_VARIANTS:
-        tp, dpw, nwin, cc = jv[:4]
-        acc0 = jv[4] if len(jv) > 4 else ACC0
-        for weighted in (False,):
-            for full in ((True,) if dpw == 4 else (False, True)):
-                parts.append(jmp_pass(tp, dpw, nwin, cc, weighted, full, acc0))
-                parts.append("\n")
-        if dpw == 4 and (tp, dpw, nwin, acc0) not in ROW_SHAPES:
-            parts.append(jmp_pass_pf(tp, dpw, nwin, cc, acc0))
+    for tp, dpw, nwin, cc, acc0, forms in JMP_VARIANTS:
+        for form in forms:
+            if form == "ahead":
+                parts.append(jmp_pass_pf(tp, dpw, nwin, cc, acc0))
+            else:
+                parts.append(jmp_pass(tp, dpw, nwin, cc, False, form == "full", acc0))
             parts.append("\n")
     parts += [
         "// The form with one block of code per row (no variant-specific rows per pass): e\n",

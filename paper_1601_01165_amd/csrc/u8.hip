@@ -563,7 +563,7 @@ __global__ __launch_bounds__(64 * NWAVE) void u8s_det_kernel(TileArgs a) {
 // used to be the default there); on 32 channels, 2048 DM trials, 200,000 samples
 // 0.40 to 0.41 ms, level with the packed sums: the 1.64 GB of output bind there.
 // ---------------------------------------------------------------------------
-template <int Q, int DPW, int NWAVE, int CC, int ROWCAP, int NBUF, bool DET>
+template <int Q, int DPW, int NWAVE, int CC, int ROWCAP, bool DET>
 __device__ __forceinline__ void u8m_tile(const TileArgs& a) {
   constexpr int ST = 256 * Q;
   constexpr int WI = DPW <= 4 ? 4 : 8;  // ints per table entry
@@ -571,7 +571,7 @@ __device__ __forceinline__ void u8m_tile(const TileArgs& a) {
   typedef int v4i __attribute__((ext_vector_type(4)));
   constexpr int LDS_BUF = 4 * CC * ROWCAP / 16;
   constexpr int LDS_DET = DET ? NWAVE * ST / 4 : 0;
-  __shared__ uint4 lds[NBUF * LDS_BUF > LDS_DET ? NBUF * LDS_BUF : LDS_DET];
+  __shared__ uint4 lds[2 * LDS_BUF > LDS_DET ? 2 * LDS_BUF : LDS_DET];
   const int nblk = a.n_time_tiles * a.n_row_tiles;
   const int W = xcd_remap(blockIdx.x, nblk);
   const int tt = W / a.n_row_tiles, rt = W % a.n_row_tiles;
@@ -596,23 +596,16 @@ __device__ __forceinline__ void u8m_tile(const TileArgs& a) {
 
   ShiftStage<NWAVE, CC, ROWCAP, 0x80808080u> stage;
   stage.load(in, a, blk, 0, min(CC, a.rows_in), t0);
-  if (NBUF == 2) {
-    stage.store(lds, min(CC, a.rows_in));
-    if (npass > 1) stage.load(in, a, blk, CC, min(CC, a.rows_in - CC), t0);
-  }
+  stage.store(lds, min(CC, a.rows_in));
+  if (npass > 1) stage.load(in, a, blk, CC, min(CC, a.rows_in - CC), t0);
   for (int p = 0; p < npass; ++p) {
     const int c0 = p * CC;
     const int ncc = min(CC, a.rows_in - c0);
     int32_t off[NI];
 #pragma unroll
     for (int k = 0; k < NI; ++k) off[k] = wav[c0 * WI + k];
-    __syncthreads();  // NBUF = 2: pass p's rows are in LDS, and every wave is done with pass p - 1's
-    if (NBUF == 1) {
-      stage.store(lds, ncc);
-      __syncthreads();
-      if (p + 1 < npass) stage.load(in, a, blk, c0 + CC, min(CC, a.rows_in - c0 - CC), t0);
-    }
-    const char* rows = reinterpret_cast<const char*>(lds + (NBUF == 2 ? (p & 1) * LDS_BUF : 0)) + 4 * lane;
+    __syncthreads();  // pass p's rows are in LDS, and every wave is done with pass p - 1's
+    const char* rows = reinterpret_cast<const char*>(lds + (p & 1) * LDS_BUF) + 4 * lane;
     // step u: two pieces of one output row with four input rows.  A step's
     // reads are issued while the step before is summed; the barriers keep the
     // compiler from hoisting more (and spilling).
@@ -643,7 +636,7 @@ __device__ __forceinline__ void u8m_tile(const TileArgs& a) {
       }
     }
     __builtin_amdgcn_sched_barrier(0);
-    if (NBUF == 2 && p + 1 < npass) {
+    if (p + 1 < npass) {
       stage.store(lds + ((p + 1) & 1) * LDS_BUF, min(CC, a.rows_in - c0 - CC));
       if (p + 2 < npass) stage.load(in, a, blk, c0 + 2 * CC, min(CC, a.rows_in - c0 - 2 * CC), t0);
     }
@@ -659,14 +652,14 @@ __device__ __forceinline__ void u8m_tile(const TileArgs& a) {
     u8_store_tile<Q, DPW, NWAVE>(a, wave, rt, beam, t0, sums, place);
 }
 
-template <int Q, int DPW, int NWAVE, int CC, int ROWCAP, int NBUF, int WPE>
+template <int Q, int DPW, int NWAVE, int CC, int ROWCAP, int WPE>
 __global__ __launch_bounds__(64 * NWAVE) __attribute__((amdgpu_waves_per_eu(WPE))) void u8m_kernel(TileArgs a) {
-  u8m_tile<Q, DPW, NWAVE, CC, ROWCAP, NBUF, false>(a);
+  u8m_tile<Q, DPW, NWAVE, CC, ROWCAP, false>(a);
 }
 
-template <int Q, int DPW, int NWAVE, int CC, int ROWCAP, int NBUF, int WPE>
+template <int Q, int DPW, int NWAVE, int CC, int ROWCAP, int WPE>
 __global__ __launch_bounds__(64 * NWAVE) __attribute__((amdgpu_waves_per_eu(WPE))) void u8m_det_kernel(TileArgs a) {
-  u8m_tile<Q, DPW, NWAVE, CC, ROWCAP, NBUF, true>(a);
+  u8m_tile<Q, DPW, NWAVE, CC, ROWCAP, true>(a);
 }
 
 // ---------------------------------------------------------------------------
@@ -702,13 +695,13 @@ __global__ __launch_bounds__(64 * NWAVE) __attribute__((amdgpu_waves_per_eu(WPE)
   X(21, 4, 8, 8, 4, 3584, false, 0) /* 64 DMs x 1024      */    \
   X(22, 4, 4, 16, 4, 3584, false, 8) /* 64 DMs x 1024, 2 blocks/CU */
 
-// Matrix-core variants: (index, Q, DPW, NWAVE, CC, ROWCAP bytes per copy, NBUF, waves per SIMD asked for)
+// Matrix-core variants: (index, Q, DPW, NWAVE, CC, ROWCAP bytes per copy, waves per SIMD asked for)
 #define U8M_VARIANTS(X)                                     \
-  X(23, 4, 4, 8, 4, 2304, 2, 4)  /* 32 DMs x 1024 */        \
-  X(24, 4, 4, 16, 4, 3584, 2, 4) /* 64 DMs x 1024 */        \
-  X(25, 2, 4, 8, 4, 1792, 2, 6)  /* 32 DMs x 512 */         \
-  X(26, 2, 2, 8, 8, 768, 2, 6)   /* 16 DMs x 512, short spans */ \
-  X(27, 2, 2, 8, 16, 1152, 2, 4) /* 16 DMs x 512, long spans */
+  X(23, 4, 4, 8, 4, 2304, 4)  /* 32 DMs x 1024 */        \
+  X(24, 4, 4, 16, 4, 3584, 4) /* 64 DMs x 1024 */        \
+  X(25, 2, 4, 8, 4, 1792, 6)  /* 32 DMs x 512 */         \
+  X(26, 2, 2, 8, 8, 768, 6)   /* 16 DMs x 512, short spans */ \
+  X(27, 2, 2, 8, 16, 1152, 4) /* 16 DMs x 512, long spans */
 
 const std::vector<Variant>& variants_u8() {
   static const std::vector<Variant> v = [] {
@@ -725,8 +718,8 @@ const std::vector<Variant>& variants_u8() {
                       KIND_TILE_U8, Q, DPW, NW, 0, CC, RC, 1, ID, WIDE ? 2 : 1});
     U8S_VARIANTS(MAKE_U8S)
 #undef MAKE_U8S
-#define MAKE_U8M(ID, Q, DPW, NW, CC, RC, NB, WPE)                                                            \
-  r.push_back(Variant{"u8m_q" #Q "_dpw" #DPW "_nw" #NW "_cc" #CC "_row" #RC "_buf" #NB, KIND_TILE_U8, Q, DPW, NW, 0, CC, RC, \
+#define MAKE_U8M(ID, Q, DPW, NW, CC, RC, WPE)                                                                \
+  r.push_back(Variant{"u8m_q" #Q "_dpw" #DPW "_nw" #NW "_cc" #CC "_row" #RC "_buf2", KIND_TILE_U8, Q, DPW, NW, 0, CC, RC, \
                       1, ID, 3});
     U8M_VARIANTS(MAKE_U8M)
 #undef MAKE_U8M
@@ -751,9 +744,9 @@ hipError_t launch_tiled_u8(const Variant& v, const TileArgs& a, dim3 grid, hipSt
   }
   U8S_VARIANTS(LAUNCH_U8S)
 #undef LAUNCH_U8S
-#define LAUNCH_U8M(ID, Q, DPW, NW, CC, RC, NB, WPE)                                         \
+#define LAUNCH_U8M(ID, Q, DPW, NW, CC, RC, WPE)                                             \
   if (v.id == ID) {                                                                         \
-    hipLaunchKernelGGL((u8m_kernel<Q, DPW, NW, CC, RC, NB, WPE>), grid, block, 0, s, a);    \
+    hipLaunchKernelGGL((u8m_kernel<Q, DPW, NW, CC, RC, WPE>), grid, block, 0, s, a);        \
     return hipGetLastError();                                                               \
   }
   U8M_VARIANTS(LAUNCH_U8M)
@@ -770,9 +763,9 @@ hipError_t launch_detect_u8(const Variant& v, const TileArgs& a, dim3 grid, hipS
   }
   U8S_VARIANTS(LAUNCH_DU8)
 #undef LAUNCH_DU8
-#define LAUNCH_DU8M(ID, Q, DPW, NW, CC, RC, NB, WPE)                                          \
+#define LAUNCH_DU8M(ID, Q, DPW, NW, CC, RC, WPE)                                              \
   if (v.id == ID) {                                                                           \
-    hipLaunchKernelGGL((u8m_det_kernel<Q, DPW, NW, CC, RC, NB, WPE>), grid, block, 0, s, a);  \
+    hipLaunchKernelGGL((u8m_det_kernel<Q, DPW, NW, CC, RC, WPE>), grid, block, 0, s, a);      \
     return hipGetLastError();                                                                 \
   }
   U8M_VARIANTS(LAUNCH_DU8M)

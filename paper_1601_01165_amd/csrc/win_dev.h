@@ -396,7 +396,6 @@ __device__ __forceinline__ void win_tile(int wave, const TileArgs& a, int tt, in
       RowPass<TP, DPW, NWIN, ROWCAP>::run(acc, row, ea, trs, toff);
     } else if constexpr (JMP) {
       // the whole pass in one block, each row's DM slots branching into static adds
-      static_assert(HasJmpPass<TP, DPW, NWIN, CC>::value, "no jump-form pass for this shape");
       if constexpr (PF)
         JmpPrefetchPass<TP, DPW, NWIN, CC, ROWCAP>::run(acc, row, ncc, ea, eb, trs, toff);
       else
