@@ -368,6 +368,17 @@ dedisp_status dedisp_batch_create(dedisp_batch* out, int32_t nbeam, const dedisp
         break;
       }
     }
+    // most of the work on rows without a pattern: slot by slot
+    const int slots = vi < 0 ? -1 : slots_variant(vi);
+    double work = 0, plain = 0;
+    for (int i = 0; i < nbeam && slots >= 0; ++i) {
+      const double w = (double)b->plans[i]->nchan * b->plans[i]->ndm * b->nsamp[i];
+      work += w;
+      plain += w * b->plans[i]->plain[0][vi];
+    }
+    bool ok = slots >= 0 && plain > kSlotsShare * work;
+    for (int i = 0; i < nbeam && ok; ++i) ok = ensure_tables(b->plans[i], 0, slots, nullptr) == DEDISP_OK;
+    if (ok) vi = slots;
   }
   if (vi < 0) {
     batch_free(b);

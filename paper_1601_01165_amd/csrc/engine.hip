@@ -109,12 +109,14 @@ const std::vector<Variant>& variants_f32() {
     std::vector<Variant> r;
 #define MAKE_F32(ID, TP, DPW, NW, NWIN, CC, RC, NB, JMP)                                                    \
   r.push_back(Variant{JMP == 2 ? "win_tp" #TP "_dpw" #DPW "_nw" #NW "_win" #NWIN "_cc" #CC "_buf" #NB "_jmpf"   \
+                      : JMP == 4 ? "win_tp" #TP "_dpw" #DPW "_nw" #NW "_win" #NWIN "_cc" #CC "_buf" #NB "_slots" \
                       : JMP    ? "win_tp" #TP "_dpw" #DPW "_nw" #NW "_win" #NWIN "_cc" #CC "_buf" #NB "_jmp"    \
                                : "win_tp" #TP "_dpw" #DPW "_nw" #NW "_win" #NWIN "_cc" #CC "_buf" #NB,         \
                       KIND_WIN_F32, TP, DPW, NW, NWIN, CC, RC, NB, ID, 0, JMP});
     F32_VARIANTS(MAKE_F32)
 #undef MAKE_F32
     lane_variants(r);
+    std::sort(r.begin(), r.end(), [](const Variant& a, const Variant& b) { return a.id < b.id; });
     return r;
   }();
   return v;

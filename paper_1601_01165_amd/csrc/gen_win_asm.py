@@ -817,9 +817,9 @@ JMP_VARIANTS = [
     (20, 4, 40, 3, 8, ()),
     (20, 4, 40, 6, 8, ()),
     (20, 4, 40, 8, 8, ("full",)),
-    (20, 4, 40, 10, 8, ()),
+    (20, 4, 40, 10, 8, ("slots",)),
     (20, 4, 44, 8, 4, ()),
-    (20, 4, 44, 10, 4, ()),
+    (20, 4, 44, 10, 4, ("slots",)),
     (20, 4, 84, 8, 4, ("ahead",)),
     (20, 4, 84, 3, 4, ("ahead",)),
     (12, 4, 32, 8, 8, ()),

@@ -48,7 +48,7 @@ struct Variant {
   int mode = 0;
   // f32 only: 1 = each row's DM slots branch into static blocks of adds; the table then holds block byte
   // offsets o * (4 * tp + 4) in place of the window offsets o; 2 = the same reading the whole window; 3 = one
-  // block of code per row
+  // block of code per row; 4 = as 1, never reading the next row's window ahead
   int jmp = 0;
   // f32, row blocks (jmp 3; gen_win_asm.py row_pass): block (m, p, o) of the code region, for offsets o,
   // o + d1, ... whose differences are m plus the bits of p (p < 7, m < row_classes, o < 4)
@@ -168,7 +168,8 @@ struct TableBuild {
 };
 hipError_t launch_build_tables(const std::vector<TableBuild>& bs, const int32_t* d_delay, int nchan, int ndm,
                                bool adjoint, int pad, hipStream_t s);
-// Whether up to kFitBatch variants fit the delay matrix: bad[k] = 0 or why not.
+// Whether up to kFitBatch variants fit the delay matrix: bad[k] = 0 or why not, and
+// bad[kFitBatch + k] = (wave tile, input row) pairs that follow no row pattern (row blocks).
 enum { kTablesWindow = 1, kTablesRow = 2, kTablesOffset = 3, kTablesPacked = 4 };
 hipError_t launch_check_fits(const std::vector<const Variant*>& vs, const int32_t* d_delay, int nchan, int ndm,
                              bool adjoint, int pad, int* bad, hipStream_t s);
@@ -215,6 +216,10 @@ int batched_blocks_per_cu(const Variant& v);
 // forward uint8, 2 adjoint); free those of direction dir other than `keep`,
 // the plan's chosen variants and pinned ones.
 dedisp_status ensure_tables(dedisp_plan p, int dir, int vi, Tables** out);
+// The variant that runs rows without a pattern slot by slot where vi has blocks for
+// those with one, or -1; and the share of such rows from which it is the faster.
+int slots_variant(int vi);
+constexpr float kSlotsShare = 0.3f;
 void drop_spare_tables(dedisp_plan p, int dir, int keep);
 
 // Timing (tune.cpp): ms per launch of fn, the median over `reps` groups of
@@ -248,8 +253,9 @@ struct dedisp_plan_s {
   std::vector<double> freq, dm;
   std::vector<int32_t> delay;       // [ndm][nchan]
   int32_t* d_delay = nullptr;       // device copy [ndm][nchan]
-  int* d_bad = nullptr;             // kFitBatch results of the fit check (after the delays)
+  int* d_bad = nullptr;             // 2 kFitBatch results of the fit check (after the delays)
   std::map<int, int> fits[3];       // per direction and variant: 0 fits, else why not
+  std::map<int, float> plain[3];    // and the share of its wave entries without a row pattern
   // adjoint view: out rows = channels, in rows = DMs, delay' = pad - delay
   int adj_pad = 0;                  // max_delay rounded up to a multiple of 4
   std::map<int, dd::Tables> fwd_f32, fwd_u8, adj_f32;

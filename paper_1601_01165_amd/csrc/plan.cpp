@@ -120,11 +120,16 @@ static dedisp_status check_fits(dedisp_plan p, int dir, const std::vector<int>& 
     const size_t n = std::min<size_t>(kFitBatch, ask.size() - k0);
     std::vector<const Variant*> list;
     for (size_t k = 0; k < n; ++k) list.push_back(&vs[ask[k0 + k]]);
-    int bad[kFitBatch];
+    int bad[2 * kFitBatch];
     hipError_t e = launch_check_fits(list, p->d_delay, p->nchan, p->ndm, dir == 2, p->adj_pad, p->d_bad, nullptr);
-    if (e == hipSuccess) e = hipMemcpy(bad, p->d_bad, n * sizeof(int), hipMemcpyDeviceToHost);
+    if (e == hipSuccess) e = hipMemcpy(bad, p->d_bad, sizeof(bad), hipMemcpyDeviceToHost);
     if (e != hipSuccess) return hip_fail(e, "checking which kernels fit");
-    for (size_t k = 0; k < n; ++k) p->fits[dir][ask[k0 + k]] = bad[k];
+    for (size_t k = 0; k < n; ++k) {
+      const Variant& v = *list[k];
+      const double waves = ((dir == 2 ? p->nchan : p->ndm) + v.dpw - 1) / v.dpw;  // those with output rows
+      p->fits[dir][v.id] = bad[k];
+      p->plain[dir][v.id] = (float)((unsigned)bad[kFitBatch + k] / (waves * rows_in));
+    }
   }
   return DEDISP_OK;
 }
@@ -195,51 +200,65 @@ dedisp_status ensure_tables(dedisp_plan p, int dir, int vi, Tables** out) {
 // 8-sample-per-lane forms took before (2.08 against 5.62 ms).
 const std::vector<int>& default_order(int dir) {
   static const std::vector<int> f32 = {35, 34, 37, 38, 36, 32, 33, 22, 28, 21, 29, 31, 23, 30, 19, 20, 39, 40, 25, 24, 27, 26, 15, 18, 13,
-                                       17, 9,  8,  16, 6,  14, 11, 7,  12, 10, 2,  3,  0,  1,  5,  4,  41, 42, 43, 46, 48, 45, 47, 44};
+                                       17, 9,  8,  16, 6,  14, 11, 7,  12, 10, 2,  3,  0,  1,  5,  4,  41, 42, 43, 46, 48, 45, 47, 44, 49, 50};
   static const std::vector<int> u8 = {22, 23, 25, 27, 26, 24, 16, 20, 15, 21, 12, 13, 17, 14, 18, 6, 2, 0, 5, 19, 9, 3, 4, 1, 8, 7, 10, 11};
   static const std::vector<int> adj = {37, 38, 39, 40, 26, 27, 32, 34, 35, 36, 33, 19, 21, 29, 20, 30, 9, 8, 6, 11, 12, 7, 10, 13, 22, 28,
-                                       18, 15, 23, 31, 17, 16, 25, 24, 14, 2, 3, 1, 0, 5, 4, 42, 41, 43, 46, 47, 45, 48, 44};
+                                       18, 15, 23, 31, 17, 16, 25, 24, 14, 2, 3, 1, 0, 5, 4, 42, 41, 43, 46, 47, 45, 48, 44, 50, 49};
   return dir == 1 ? u8 : dir == 2 ? adj : f32;
 }
 
+// Rows whose delays follow no pattern (DM lists or channels in descending order, shuffled
+// or very uneven lists) cost a row-block variant its slots and the way there, 1.2
+// times its time on regular lists, where the jump form takes 1.06 whatever the list
+// (1024 channels, 2000 DM trials, 20,000 samples: 0.95 ms in row blocks, 1.12 with the DM
+// list reversed, 1.01 slot by slot; backward, 1024 DM trials, channels in descending order:
+// 0.80, 0.97 and 0.84).  Every row was a slot's when row blocks came in, so the
+// jump form is kept for these lists.
+int slots_variant(int vi) { return vi == 35 ? 49 : vi == 37 ? 50 : -1; }
+
 // The choice by size.  A plan that was not tuned keeps, beside its default
 // variant, a few with smaller tiles, and each call takes the one with the least
-// estimated time per input row,
-//   max(alone, rounds * full),   rounds = ceil(blocks / CUs),
-// in microseconds measured on MI355X: `alone` with at most one block per CU (the
+// estimated time,
+//   input rows * max(alone, rounds * full) * (1 + chain * s),   rounds = ceil(blocks / CUs),
+// with us per input row measured on MI355X: `alone` with at most one block per CU (the
 // latency of a row's step), `full` a block's share of a CU that holds as many as
-// fit.  The coarse tiles have the best throughput (64 DM trials x 1280 samples:
-// 39 adds per ns over the chip; 16 x 256 in LDS: 17), the fine ones occupy the chip
+// fit; s is the share of rows without a pattern.  The coarse tiles have the best
+// throughput (64 DM trials x 1280 samples: 39 adds per ns over the chip; 16 x 256 in LDS:
+// 17), the fine ones occupy the chip
 // with little work: 1024 channels, 301 DM trials, 2003 samples are 10 coarse
 // tiles in 473 us or 304 fine ones in 103 us, while 370 channels, 1072 DM trials,
 // 11,790 samples are 170 coarse tiles in 193 us and 315 us in fine ones.  Tiles of
 // 48 DM trials (3 waves per SIMD, 0.85 of the coarse tile's time) take the calls
-// that would leave the last round of coarse tiles half empty (3 beams of 768
-// channels, 1001 DM trials, 9973 samples: 752 against 775 us), and tiles of 32 x
+// that would leave the last round of coarse tiles half empty, and tiles of 32 x
 // 768 those between the sizes (two blocks per CU share one's waits: 2 beams of 264
 // channels, 239 DM trials, 18,314 samples take 106 us, 132 us in coarse tiles and 153
-// in LDS; backward 93, 125 and 170).  Over 18 random shapes each way the variant
-// chosen is 1 % from the fastest on average, and 15 % at most.
+// in LDS; backward 93, 125 and 170).
 struct SizeCost {
   int vi;
-  float alone, full;
+  float alone, full, chain;
 };
 static const std::vector<SizeCost>& size_costs(int dir) {
-  static const std::vector<SizeCost> f32 = {{35, .45f, .478f}, {41, .40f, .405f}, {43, .28f, .195f}, {44, .100f, .036f}, {45, .132f, .061f}};
-  static const std::vector<SizeCost> u8 = {{22, .50f, .51f},  {23, .27f, .207f},
-                                           {25, .18f, .125f}, {26, .13f, .079f}, {27, .14f, .150f}};
-  static const std::vector<SizeCost> adj = {{37, .45f, .478f}, {42, .40f, .405f}, {39, .44f, .440f}, {43, .28f, .195f}, {44, .100f, .036f}, {46, .178f, .125f}};
+  static const std::vector<SizeCost> f32 = {{35, .45f, .478f, .2f},  {41, .40f, .405f, .27f}, {43, .28f, .195f, .42f},
+                                            {44, .100f, .036f, 0.f}, {45, .132f, .061f, 0.f}};
+  static const std::vector<SizeCost> u8 = {{22, .50f, .51f, 0.f},  {23, .27f, .207f, 0.f}, {25, .18f, .125f, 0.f},
+                                           {26, .13f, .079f, 0.f}, {27, .14f, .150f, 0.f}};
+  static const std::vector<SizeCost> adj = {{37, .45f, .478f, .2f},  {50, .47f, .440f, 0.f},
+                                            {42, .40f, .405f, .27f}, {39, .44f, .440f, 0.f},
+                                            {43, .28f, .195f, .42f}, {44, .100f, .036f, 0.f}, {46, .178f, .125f, 0.f}};
   return dir == 1 ? u8 : dir == 2 ? adj : f32;
 }
 
+static int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
+
 static float size_cost(dedisp_plan p, int dir, const Variant& v, int nbeam, int64_t nout) {
   // variants without a measured pair (wide spans): the coarse tile's rate, scaled by the tile
-  SizeCost c = {v.id, .47f, .508f * (float)(v.dt() * v.st()) / (64 * 1280)};
+  SizeCost c = {v.id, .47f, .508f * (float)(v.dt() * v.st()) / (64 * 1280), 0.f};
   for (const SizeCost& k : size_costs(dir))
     if (k.vi == v.id) c = k;
-  const int64_t rows_out = dir == 2 ? p->nchan : p->ndm;
-  const int64_t blocks = (rows_out + v.dt() - 1) / v.dt() * ((nout + v.st() - 1) / v.st()) * nbeam;
-  return std::max(c.alone, (float)((blocks + p->ncu - 1) / p->ncu) * c.full);
+  const int64_t rows_out = dir == 2 ? p->nchan : p->ndm, rows_in = dir == 2 ? p->ndm : p->nchan;
+  const int64_t blocks = ceil_div(rows_out, v.dt()) * ceil_div(nout, v.st()) * nbeam;
+  const float s = c.chain > 0.f ? p->plain[dir][v.id] : 0.f;
+  return rows_in * std::max(c.alone, (float)ceil_div(blocks, p->ncu) * c.full) * (1.f + c.chain * s);
 }
 
 // The variant a call of nbeam x nout output samples runs (-1: direct).
@@ -251,8 +270,7 @@ static int pick_variant(dedisp_plan p, int dir, int nbeam, int64_t nout) {
   // default uint8 shape are as fast as any (0.40 ms against 0.41 to 0.44 ms on 32
   // channels, 2048 DM trials, 200,000 samples)
   const Variant& mv = vs[main];
-  if (dir == 1 && mv.mode == 1 &&
-      (int64_t)((p->ndm + mv.dt() - 1) / mv.dt()) * ((nout + mv.st() - 1) / mv.st()) * nbeam >= 16 * (int64_t)p->ncu)
+  if (dir == 1 && mv.mode == 1 && ceil_div(p->ndm, mv.dt()) * ceil_div(nout, mv.st()) * nbeam >= 16 * (int64_t)p->ncu)
     return main;
   int best = main;
   float least = size_cost(p, dir, mv, nbeam, nout);
@@ -287,16 +305,21 @@ static void ensure_chosen(dedisp_plan p, int dir) {
   }
   p->by_size[dir] = true;
   p->fine[dir].clear();
+  const int blocks = first;  // the row blocks' variant, if it is one
+  const int slots = dir == 1 ? -1 : slots_variant(first);
+  if (slots >= 0 && p->plain[dir][first] > kSlotsShare && check_fits(p, dir, {slots}) == DEDISP_OK &&
+      p->fits[dir][slots] == 0)
+    first = slots;
   v = first;
   if (first < 0) return;
   std::vector<int> build = {first};
   for (const SizeCost& c : size_costs(dir))
-    if (c.vi != first && p->fits[dir][c.vi] == 0) build.push_back(c.vi);
+    if (c.vi != first && c.vi != blocks && c.vi != slots && p->fits[dir][c.vi] == 0) build.push_back(c.vi);
+  const std::vector<int> all = build;
   std::map<int, Tables>& m = dir == 0 ? p->fwd_f32 : dir == 1 ? p->fwd_u8 : p->adj_f32;
   build.erase(std::remove_if(build.begin(), build.end(), [&](int vi) { return m.count(vi) != 0; }), build.end());
   if (build.empty() || build_tables(p, dir, build) == DEDISP_OK) {
-    for (const SizeCost& c : size_costs(dir))
-      if (c.vi != first && m.count(c.vi)) p->fine[dir].push_back(c.vi);
+    p->fine[dir].assign(all.begin() + 1, all.end());
   } else if (ensure_tables(p, dir, first, nullptr) != DEDISP_OK) {
     v = -1;
   }
@@ -479,7 +502,7 @@ dedisp_status dedisp_plan_create(dedisp_plan* plan, int32_t nchan, const double*
   hipError_t e = hipGetDevice(&p->device);
   if (e == hipSuccess) e = hipDeviceGetAttribute(&p->ncu, hipDeviceAttributeMultiprocessorCount, p->device);
   if (e == hipSuccess && p->ncu < 1) p->ncu = 1;
-  if (e == hipSuccess) e = hipMalloc(&p->d_delay, (p->delay.size() + kFitBatch) * sizeof(int32_t));
+  if (e == hipSuccess) e = hipMalloc(&p->d_delay, (p->delay.size() + 2 * kFitBatch) * sizeof(int32_t));
   if (e == hipSuccess)
     e = hipMemcpy(p->d_delay, p->delay.data(), p->delay.size() * sizeof(int32_t), hipMemcpyHostToDevice);
   if (e != hipSuccess) {

@@ -29,9 +29,9 @@ struct Column {
 };
 
 // The wave entries of this thread's waves; returns why they do not fit the variant, or
-// 0, and what the waves need staged.
+// 0, what the waves need staged, and how many of them follow no row pattern.
 __device__ int table_waves(const Variant& v, const DelayView& delay, int rows_out, int rows_in, int rt, int c, int sbase,
-                           int32_t* wav, int& need) {
+                           int32_t* wav, int& need, int& plain) {
   const int DT = v.nwave * v.dpw, WI = v.wav_ints();
   // rows past the end repeat the last row (their results are not stored)
   auto d = [&](int k) { return delay(min(rt * DT + k, rows_out - 1), c); };
@@ -59,11 +59,13 @@ __device__ int table_waves(const Variant& v, const DelayView& delay, int rows_ou
         }
         const int nl = max(v.tp / 4 + 1, (v.tp + maxo + 3) / 4);
         need = max(need, ws + 63 * v.tp + 4 * nl);
+        const int o0 = packed & 0xff;
+        const bool pattern = m >= 0 && top - m <= 1 && m < v.row_classes() && o0 < 4;
+        plain += pattern ? 0 : 1;
         if (!e) continue;
         const bool last = c % v.cc == v.cc - 1 || c == rows_in - 1;
-        const int o0 = packed & 0xff;
         int target = 0;
-        if (!last && m >= 0 && top - m <= 1 && m < v.row_classes() && o0 < 4) {
+        if (!last && pattern) {
           for (int j = 1; j < v.dpw; ++j)
             p |= ((packed >> (8 * j) & 0xff) - (packed >> (8 * j - 8) & 0xff) - m) << (j - 1);
           target = v.row_block(m, p, o0);
@@ -135,9 +137,9 @@ __device__ int table_waves(const Variant& v, const DelayView& delay, int rows_ou
 }
 
 // The tables' entries of input row c for row tile rt (not written when blk and wav are
-// null); returns why they do not fit the variant, or 0.  Every thread of the block calls it.
+// null); returns why they do not fit the variant, or 0 (see table_waves).  Every thread of the block calls it.
 __device__ int table_columns(const Variant& v, const DelayView& delay, int rows_out, int rows_in, int rt, int c,
-                             int32_t* blk, int32_t* wav) {
+                             int32_t* blk, int32_t* wav, int& plain) {
   __shared__ Column col;
   const int lane = threadIdx.x % kCols, slice = threadIdx.x / kCols;
   const bool live = c < rows_in;
@@ -149,7 +151,7 @@ __device__ int table_columns(const Variant& v, const DelayView& delay, int rows_
   for (int s = 0; s < kSlices; ++s) dmin = min(dmin, col.dmin[s][lane]);
   const int sbase = v.kind == KIND_TILE_U8 ? dmin & ~15 : dmin & ~3;
   int need = 0;
-  int why = live ? table_waves(v, delay, rows_out, rows_in, rt, c, sbase, wav, need) : 0;
+  int why = live ? table_waves(v, delay, rows_out, rows_in, rt, c, sbase, wav, need, plain) : 0;
   col.need[slice][lane] = need;
   __syncthreads();
   for (int s = 0; s < kSlices; ++s) need = max(need, col.need[s][lane]);
@@ -174,10 +176,12 @@ __global__ __launch_bounds__(256) void build_tables_kernel(BuildList list, Delay
   const int c = (blockIdx.x - rt * ncb) * kCols + threadIdx.x % kCols;
   if (blockIdx.x == 0)
     for (int k = threadIdx.x; k < b.slack; k += 256) b.wav[b.ent + k] = 0;
-  if (rt * b.v.dt() < rows_out) (void)table_columns(b.v, delay, rows_out, rows_in, rt, c, b.blk, b.wav);
+  int plain = 0;
+  if (rt * b.v.dt() < rows_out) (void)table_columns(b.v, delay, rows_out, rows_in, rt, c, b.blk, b.wav, plain);
 }
 
-// Whether the variants fit: bad[k] (zero before) becomes the reason if variant k does not.
+// Whether the variants fit: bad[k] (zero before) becomes the reason if variant k does not;
+// bad[kFitBatch + k] counts the wave entries that follow no row pattern.
 struct VariantList {
   Variant v[kFitBatch];
 };
@@ -188,8 +192,10 @@ __global__ __launch_bounds__(256) void check_fits_kernel(VariantList list, Delay
   const int rt = blockIdx.x / ncb;
   const int c = (blockIdx.x - rt * ncb) * kCols + threadIdx.x % kCols;
   if (rt * v.dt() >= rows_out) return;
-  const int why = table_columns(v, delay, rows_out, rows_in, rt, c, nullptr, nullptr);
+  int plain = 0;
+  const int why = table_columns(v, delay, rows_out, rows_in, rt, c, nullptr, nullptr, plain);
   if (why) atomicMax(bad + blockIdx.y, why);
+  if (plain) atomicAdd(bad + kFitBatch + blockIdx.y, plain);
 }
 
 // Adjoint: per (row tile, pass) the least start and greatest end of the
@@ -250,7 +256,7 @@ hipError_t launch_check_fits(const std::vector<const Variant*>& vs, const int32_
   }
   const int64_t grid = nrt * ((rows_in + kCols - 1) / kCols);
   if (grid > 0x7fffffff) return hipErrorInvalidConfiguration;
-  hipError_t e = hipMemsetAsync(bad, 0, vs.size() * sizeof(int), s);
+  hipError_t e = hipMemsetAsync(bad, 0, 2 * kFitBatch * sizeof(int), s);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(check_fits_kernel, dim3((unsigned)grid, (unsigned)vs.size()), dim3(256), 0, s, list,
                      DelayView{d_delay, nchan, adjoint, pad}, rows_out, rows_in, bad);

@@ -499,7 +499,8 @@ void win_persistent(const BeamDesc* __restrict__ beams,
 //  CC rows per LDS pass, ROWCAP floats per LDS row, NBUF LDS buffers, JMP)
 // JMP = 1: each row's DM slots branch into static blocks of adds (JmpPass)
 // instead of indexing the window registers; JMP = 2: the same, every row
-// reading the whole window (no per-row read-count branches).
+// reading the whole window (no per-row read-count branches); JMP = 3: one block of
+// code per row (RowPass); JMP = 4: as 1 without the next row's window read ahead.
 // A lane owns TP consecutive samples; TP/4 odd (12, 20, 28, 36) keeps its
 // 16-byte LDS reads free of bank conflicts.
 #define F32_VARIANTS(X)                                          \
@@ -546,6 +547,8 @@ void win_persistent(const BeamDesc* __restrict__ beams,
   X(40, 20, 4, 4, 84, 3, 1792, 2, 1)  /* 16 DMs x 1280, jump, wide spans, 3 waves/SIMD */ \
   X(41, 20, 4, 12, 40, 10, 1792, 2, 3) /* 48 DMs x 1280, row blocks */ \
   X(42, 20, 4, 12, 44, 10, 1792, 2, 3) /* 48 DMs x 1280, row blocks */ \
-  X(43, 12, 4, 8, 32, 8, 1024, 2, 3) /* 32 DMs x 768, row blocks */
+  X(43, 12, 4, 8, 32, 8, 1024, 2, 3) /* 32 DMs x 768, row blocks */ \
+  X(49, 20, 4, 16, 40, 10, 1792, 2, 4) /* 64 DMs x 1280, jump: 35 for lists without row patterns */ \
+  X(50, 20, 4, 16, 44, 10, 1792, 2, 4) /* 64 DMs x 1280, jump: 37 for lists without row patterns */
 
 }  // namespace dd
