@@ -116,9 +116,9 @@ dedisp_status dedisp_plan_prepare(dedisp_plan plan, dedisp_dtype in_type, int32_
  * Beams share the plan's delays and weights.  Uses the plan's kernel variant
  * for this dtype when one was chosen by dedisp_autotune or
  * dedisp_plan_set_variant, otherwise the default (dedisp_plan_variant) or one
- * of a few finer-tiled variants prepared with it, whichever is estimated to be
- * fastest for nbeam x nsamp; falls back to a direct (untiled) kernel when no
- * tiled variant fits the plan's delay spans.  Asynchronous on `stream`.
+ * of a few finer-tiled variants prepared with it, or (float32) the direct, untiled
+ * kernel, whichever is estimated to be fastest for nbeam x nsamp; the direct kernel
+ * also where no tiled variant fits the plan's delay spans.  Asynchronous on `stream`.
  * Errors: DEDISP_E_INVALID (NULL plan or pointer, nbeam < 1, nsamp < 1),
  * DEDISP_E_DTYPE, DEDISP_E_SHAPE (in_stride < nsamp + max_delay,
  * out_stride < nsamp, rows longer than 2^29 samples, or more than 65535
@@ -364,7 +364,7 @@ dedisp_status dedisp_plan_set_variant(dedisp_plan plan, dedisp_dtype in_type, in
 
 /* Variant chosen for in_type (-1 = direct kernel): the one set or tuned, else
  * the default, which calls too small to fill the GPU with it replace by a
- * finer-tiled one. */
+ * finer-tiled one, or by the direct kernel. */
 int32_t dedisp_plan_variant(dedisp_plan plan, dedisp_dtype in_type);
 
 /* The same for the adjoint (float32 variants; -1 = direct adjoint kernel). */

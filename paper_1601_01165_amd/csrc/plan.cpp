@@ -219,7 +219,7 @@ int slots_variant(int vi) { return vi == 35 ? 49 : vi == 37 ? 50 : -1; }
 // The choice by size.  A plan that was not tuned keeps, beside its default
 // variant, a few with smaller tiles, and each call takes the one with the least
 // estimated time,
-//   input rows * max(alone, rounds * full) * (1 + chain * s),   rounds = ceil(blocks / CUs),
+//   2 us + input rows * max(alone, rounds * full) * (1 + chain * s),   rounds = ceil(blocks / CUs),
 // with us per input row measured on MI355X: `alone` with at most one block per CU (the
 // latency of a row's step), `full` a block's share of a CU that holds as many as
 // fit; s is the share of rows without a pattern.  The coarse tiles have the best
@@ -232,19 +232,24 @@ int slots_variant(int vi) { return vi == 35 ? 49 : vi == 37 ? 50 : -1; }
 // that would leave the last round of coarse tiles half empty, and tiles of 32 x
 // 768 those between the sizes (two blocks per CU share one's waits: 2 beams of 264
 // channels, 239 DM trials, 18,314 samples take 106 us, 132 us in coarse tiles and 153
-// in LDS; backward 93, 125 and 170).
+// in LDS; backward 93, 125 and 170).  The wide lane tiles (48) are kept where delay spans
+// leave no other lane kernel (backward, 30 channels x 102 DM trials x 2162 samples: 18.5
+// us, 61 in the default's wide windows), and the direct kernel, which stages nothing, takes
+// the calls of a few rows (12 channels, 18 DM trials, 2793 samples backward: 6.7 us, 8.6).
 struct SizeCost {
   int vi;
   float alone, full, chain;
 };
+static constexpr int kWideLanes = 48;
 static const std::vector<SizeCost>& size_costs(int dir) {
   static const std::vector<SizeCost> f32 = {{35, .45f, .478f, .2f},  {41, .40f, .405f, .27f}, {43, .28f, .195f, .42f},
-                                            {44, .100f, .036f, 0.f}, {45, .132f, .061f, 0.f}};
+                                            {44, .100f, .036f, 0.f}, {45, .132f, .061f, 0.f}, {kWideLanes, .14f, .14f, 0.f}};
   static const std::vector<SizeCost> u8 = {{22, .50f, .51f, 0.f},  {23, .27f, .207f, 0.f}, {25, .18f, .125f, 0.f},
                                            {26, .13f, .079f, 0.f}, {27, .14f, .150f, 0.f}};
   static const std::vector<SizeCost> adj = {{37, .45f, .478f, .2f},  {50, .47f, .440f, 0.f},
                                             {42, .40f, .405f, .27f}, {39, .44f, .440f, 0.f},
-                                            {43, .28f, .195f, .42f}, {44, .100f, .036f, 0.f}, {46, .178f, .125f, 0.f}};
+                                            {43, .28f, .195f, .42f}, {44, .100f, .036f, 0.f}, {46, .178f, .125f, 0.f},
+                                            {kWideLanes, .14f, .145f, 0.f}};
   return dir == 1 ? u8 : dir == 2 ? adj : f32;
 }
 
@@ -258,7 +263,14 @@ static float size_cost(dedisp_plan p, int dir, const Variant& v, int nbeam, int6
   const int64_t rows_out = dir == 2 ? p->nchan : p->ndm, rows_in = dir == 2 ? p->ndm : p->nchan;
   const int64_t blocks = ceil_div(rows_out, v.dt()) * ceil_div(nout, v.st()) * nbeam;
   const float s = c.chain > 0.f ? p->plain[dir][v.id] : 0.f;
-  return rows_in * std::max(c.alone, (float)ceil_div(blocks, p->ncu) * c.full) * (1.f + c.chain * s);
+  return 2.f + rows_in * std::max(c.alone, (float)ceil_div(blocks, p->ncu) * c.full) * (1.f + c.chain * s);
+}
+
+// The direct kernel's (float32): a term's latency, or with several blocks of 256 outputs per CU its share.
+static float direct_cost(dedisp_plan p, int dir, int nbeam, int64_t nout) {
+  const int64_t rows_out = dir == 2 ? p->nchan : p->ndm, rows_in = dir == 2 ? p->ndm : p->nchan;
+  const float blocks = (float)(rows_out * ceil_div(nout, 256) * nbeam);
+  return rows_in * std::max(dir == 2 ? .233f : .13f, blocks / p->ncu * .065f);
 }
 
 // The variant a call of nbeam x nout output samples runs (-1: direct).
@@ -281,7 +293,7 @@ static int pick_variant(dedisp_plan p, int dir, int nbeam, int64_t nout) {
       best = vi;
     }
   }
-  return best;
+  return dir != 1 && direct_cost(p, dir, nbeam, nout) < least ? -1 : best;
 }
 
 static bool aligned16(const void* ptr) { return ((uintptr_t)ptr & 15u) == 0; }
@@ -313,8 +325,14 @@ static void ensure_chosen(dedisp_plan p, int dir) {
   v = first;
   if (first < 0) return;
   std::vector<int> build = {first};
+  bool lanes = false;  // a lane kernel fits
+  auto wanted = [&](const SizeCost& c) {
+    if (c.vi == first || c.vi == blocks || c.vi == slots || p->fits[dir][c.vi] != 0 || (c.vi == kWideLanes && lanes && dir != 1)) return false;
+    lanes |= dir != 1 && variants_f32()[c.vi].kind == KIND_LANE_F32;
+    return true;
+  };
   for (const SizeCost& c : size_costs(dir))
-    if (c.vi != first && c.vi != blocks && c.vi != slots && p->fits[dir][c.vi] == 0) build.push_back(c.vi);
+    if (wanted(c)) build.push_back(c.vi);
   const std::vector<int> all = build;
   std::map<int, Tables>& m = dir == 0 ? p->fwd_f32 : dir == 1 ? p->fwd_u8 : p->adj_f32;
   build.erase(std::remove_if(build.begin(), build.end(), [&](int vi) { return m.count(vi) != 0; }), build.end());
