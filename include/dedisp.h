@@ -283,7 +283,8 @@ dedisp_status dedisp_batch_destroy(dedisp_batch batch);
  * none fits, dedisperses into the workspace and searches the stored rows, some
  * beams at a time: their series and records take at most 1 GiB, or one beam's,
  * and no more than the workspace has room for.  float32 beams that alone take
- * more than either are searched in place if a variant fits.
+ * more than either, and large calls of few channels, are searched in place if a
+ * variant fits.
  * The forward variant (dedisp_plan_set_variant, dedisp_autotune) only serves the
  * unfused path.  Asynchronous on
  * `stream`; the first call of a plan and dtype may build tile tables

@@ -32,8 +32,10 @@ static bool det_fits(dedisp_plan p, bool u8, int vi) {
 // (-1: unfused), otherwise the automatic choice.
 //   float32: unfused.  Storing the series and searching them costs about 0.05 ms
 //     on the 1024-channel, 2000-DM beam; the fused forms lose more by their
-//     registers and overlapping tiles (1.10 ms unfused, 1.27 ms the best fused).  Where
-//     one beam's series alone take more than 1 GiB: fused, if a variant fits.
+//     registers and overlapping tiles (1.10 ms unfused, 1.27 ms the best fused).  On few
+//     channels the series cost more than the sums (8 beams of 22 channels, 2121 DM
+//     trials, 11,614 samples: 606 us unfused, 366 fused), and where one beam's series
+//     take more than 1 GiB, the memory: fused then, if a variant fits (search_path).
 //   uint8: the first that fits from a preference list (fastest first on the
 //     32-channel, 2048-DM beam: the int32 series would be 1.64 GB), or with
 //     fewer blocks than CUs the same kernel with half the samples per tile
@@ -67,8 +69,10 @@ static size_t fused_ws(dedisp_plan p, const Variant& v, int nbeam, int nsamp) {
 static constexpr size_t kUnfusedBytes = (size_t)1 << 30;
 static constexpr size_t kUnfusedSlack = 256;  // the records start on the next multiple of this
 
+static size_t beam_series(dedisp_plan p, int nsamp) { return (size_t)p->ndm * round_up(nsamp, 4) * 4; }
+
 static size_t unfused_beam_ws(dedisp_plan p, int nsamp) {
-  return (size_t)p->ndm * (round_up(nsamp, 4) * 4 + rows_tiles(nsamp) * sizeof(DetRec));
+  return beam_series(p, nsamp) + (size_t)p->ndm * rows_tiles(nsamp) * sizeof(DetRec);
 }
 
 static size_t unfused_ws(dedisp_plan p, int nbeam, int nsamp) {
@@ -84,13 +88,31 @@ static int unfused_beams(dedisp_plan p, int nbeam, int nsamp, size_t ws_bytes) {
   return (int)std::min({(size_t)nbeam, most, (ws_bytes - kUnfusedSlack) / beam});
 }
 
-// The variant that searches float32 beams in place where their series are too
-// large for the workspace, or -1.
+// Few channels: below this many the fused search is the faster from this much
+// of series on (over 150 random calls of 8 to 160 channels it is never more than 3 %
+// behind the fused one of before, and 13 % faster on average than always unfused; 73
+// channels, 40 beams of 670 DM trials, 9995 samples: 979 and 1211 us; 16 channels, 100 DM
+// trials, 5000 samples: 22 and 11 us).
+static constexpr int kFewChannels = 96;
+static constexpr size_t kFewBytes = (size_t)16 << 20;
+
+// The variant that searches float32 beams in place, or -1.
 static int f32_in_place(dedisp_plan p) {
-  static const int pref_f32[] = {42, 41, 39, 16, 14, 18, 13, 15, 17};
-  for (int k : pref_f32)
-    if (det_fits(p, false, k)) return k;
+  static const int few[] = {20, 16, 14, 18, 13, 15, 17, 39}, many[] = {42, 41, 39, 16, 14, 18, 13, 15, 17};
+  if (p->nchan < kFewChannels) {
+    for (int k : few)
+      if (det_fits(p, false, k)) return k;
+  } else {
+    for (int k : many)
+      if (det_fits(p, false, k)) return k;
+  }
   return -1;
+}
+
+// Whether float32 calls of these sizes go in place if they can.
+static bool f32_prefers_in_place(dedisp_plan p, int nbeam, int nsamp) {
+  const size_t beam = beam_series(p, nsamp);
+  return beam > kUnfusedBytes || (p->nchan < kFewChannels && nbeam * beam > kFewBytes);
 }
 
 // uint8: the small tile beside the default variant vi, or -1.  Looked at on the
@@ -114,9 +136,8 @@ static bool search_path(dedisp_plan p, bool u8, int nbeam, int nsamp, size_t ws_
       if (blocks < p->ncu && ws_bytes >= fused_ws(p, vs[small], nbeam, nsamp)) vi = small;
     }
   } else if (vi < 0 && p->var_det_f32 < -1) {
-    // beams larger than a group, or than the workspace (sized for such): in place
-    if (unfused_beam_ws(p, nsamp) > std::min(kUnfusedBytes, ws_bytes - std::min(ws_bytes, kUnfusedSlack)))
-      vi = f32_in_place(p);
+    // in place too where the workspace (sized for such a call) is too small for one beam's series
+    if (f32_prefers_in_place(p, nbeam, nsamp) || unfused_beams(p, nbeam, nsamp, ws_bytes) == 0) vi = f32_in_place(p);
   }
   if (vi >= 0) return ws_bytes >= fused_ws(p, vs[vi], nbeam, nsamp);
   beams = unfused_beams(p, nbeam, nsamp, ws_bytes);
@@ -126,9 +147,14 @@ static bool search_path(dedisp_plan p, bool u8, int nbeam, int nsamp, size_t ws_
 static size_t search_ws(dedisp_plan p, bool u8, int nbeam, int nsamp) {
   const std::vector<Variant>& vs = u8 ? variants_u8() : variants_f32();
   int vi = det_variant(p, u8);
-  if (!u8 && vi < 0 && p->var_det_f32 < -1 && unfused_beam_ws(p, nsamp) > kUnfusedBytes) vi = f32_in_place(p);
+  size_t n = 0;
+  if (!u8 && vi < 0 && p->var_det_f32 < -1 && f32_prefers_in_place(p, nbeam, nsamp)) {
+    vi = f32_in_place(p);
+    // few channels: room for the series too, which a smaller call stores
+    if (beam_series(p, nsamp) <= kUnfusedBytes) n = unfused_ws(p, nbeam, nsamp);
+  }
   if (vi < 0) return unfused_ws(p, nbeam, nsamp);
-  size_t n = fused_ws(p, vs[vi], nbeam, nsamp);
+  n = std::max(n, fused_ws(p, vs[vi], nbeam, nsamp));
   const int small = u8 ? u8_small_tile(p, vi) : -1;
   if (small >= 0) {
     // The small tile's records too, as far as a call with fewer blocks than CUs can need

@@ -46,12 +46,12 @@ def _same(got, want):
 
 
 @pytest.mark.parametrize("u8,nc,nd", [(True, 16, 256), (True, 16, 33), (True, 1100, 40), (False, 128, 2048),
-                                      (False, 128, 30)])
+                                      (False, 128, 30), (False, 16, 300), (False, 16, 2048)])
 def test_size_grows_with_the_call(u8, nc, nd):
     """Up to the series that fit one group, the size asked for never falls as beams or samples grow."""
     L, plan = _dd().lib(), _plan(nc, nd, 0.05)
     beams = [1, 2, 3, 7, 8, 40]
-    most = 120000 if nd == 2048 else 1000000
+    most = min(1000000, (1 << 28) // nd - 4)  # 1 GiB of series per beam
     sizes = sorted({1, 3, 991, 992, 993, 18700, 20000, 30752, 31744, 31745} | set(range(1, most, most // 97)))
     asked = np.array([[L.dedisp_detect_workspace_bytes(plan.handle, int(u8), nb, ns) for ns in sizes] for nb in beams])
     assert (asked > 0).all()
@@ -86,6 +86,22 @@ def test_f32_shorter_calls(nb, long, short):
         _same(dd.detect(x, plan, nsamp=ns, workspace=mine), got)
         assert torch.cuda.max_memory_allocated() - before < 1 << 22
         _same(dd.detect(x, plan, nsamp=ns, workspace=mine[:16]), got)
+
+
+@pytest.mark.parametrize("nd", [300, 2048])
+def test_f32_few_channels(nd):
+    """On few channels large calls are searched in place: they run with room for the records alone (64
+    bytes per series and tile of at least 1000 samples), and so do the shorter ones."""
+    dd, plan = _dd(), _plan(16, nd, 0.01)
+    long = 60000000 // nd // 3
+    x = dd.empty_rows(3, 16, long + plan.max_delay, torch.float32, "cuda")
+    x.copy_(torch.randint(-3, 4, x.shape, device="cuda"))
+    plain = _plan(16, nd, 0.01)
+    plain.set_detect_variant(-1)
+    for ns in (long, long // 14, long // 15, 100, 1):
+        got = _detect(plan, x, ns, 3 * nd * (long // 1000 + 1) * 64)
+        _same(got, dd.detect(x, plan, nsamp=ns))
+        _same(got, dd.detect(x, plain, nsamp=ns))
 
 
 def test_autotune_times_every_fused_variant_of_a_large_call():
