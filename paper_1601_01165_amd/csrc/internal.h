@@ -90,7 +90,7 @@ const std::vector<int>& default_order(int dir);
 struct Tables {
   int variant = -1;
   int n_row_tiles = 0;
-  std::shared_ptr<void> mem;  // the device memory they lie in (several variants' may share it)
+  std::shared_ptr<void> mem;  // the device memory they lie in (small tables of several variants share it)
   int32_t* d_blk = nullptr;
   int32_t* d_wav = nullptr;
   int32_t* d_span = nullptr;  // adjoint: per (row tile, pass) {least stage base, greatest stage end}

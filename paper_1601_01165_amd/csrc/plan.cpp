@@ -135,31 +135,42 @@ static dedisp_status check_fits(dedisp_plan p, int dir, const std::vector<int>& 
 }
 
 // Build the tables of the variants `ids` (each fits, none is built yet) in direction
-// `dir` in one allocation and one launch, complete for every stream on return.
+// `dir` in one launch, complete for every stream on return.  Tables of 256 KiB and
+// more lie in an allocation of their own, so that dropping them gives it back; smaller
+// ones share one (an allocation costs more than building them).
 static dedisp_status build_tables(dedisp_plan p, int dir, const std::vector<int>& ids) {
   std::map<int, Tables>& m = dir == 0 ? p->fwd_f32 : dir == 1 ? p->fwd_u8 : p->adj_f32;
   const std::vector<Variant>& vs = dir == 1 ? variants_u8() : variants_f32();
-  size_t total = 0, at = 0;
-  for (int vi : ids) total += table_sizes(p, dir, vs[vi]).total();
-  std::shared_ptr<void> mem;
-  hipError_t e = shared_malloc(mem, total * sizeof(int32_t));
-  if (e != hipSuccess) return fail(DEDISP_E_NOMEM, "device allocation of tile tables failed");
+  constexpr size_t kOwn = (256 << 10) / sizeof(int32_t);
+  size_t small = 0, at = 0;
+  for (int vi : ids) {
+    const size_t n = table_sizes(p, dir, vs[vi]).total();
+    if (n < kOwn) small += n;
+  }
+  std::shared_ptr<void> common;
+  hipError_t e = small ? shared_malloc(common, small * sizeof(int32_t)) : hipSuccess;
   std::vector<Tables> built;
   std::vector<TableBuild> bs;
-  for (int vi : ids) {
-    const Variant& v = vs[vi];
+  for (size_t k = 0; k < ids.size() && e == hipSuccess; ++k) {
+    const Variant& v = vs[ids[k]];
     const TableSizes n = table_sizes(p, dir, v);
     Tables t;
-    t.variant = vi;
+    t.variant = ids[k];
     t.n_row_tiles = ((dir == 2 ? p->nchan : p->ndm) + v.dt() - 1) / v.dt();
-    t.mem = mem;
-    t.d_blk = static_cast<int32_t*>(mem.get()) + at;
+    if (n.total() < kOwn) {
+      t.mem = common;
+      t.d_blk = static_cast<int32_t*>(common.get()) + at;
+      at += n.total();
+    } else {
+      e = shared_malloc(t.mem, n.total() * sizeof(int32_t));
+      t.d_blk = static_cast<int32_t*>(t.mem.get());
+    }
     t.d_wav = t.d_blk + n.blk;
     if (n.span) t.d_span = t.d_wav + n.ent + n.slack;
-    at += n.total();
     built.push_back(t);
     bs.push_back({v, t.d_blk, t.d_wav, t.d_span, n.ent, n.slack});
   }
+  if (e != hipSuccess) return fail(DEDISP_E_NOMEM, "device allocation of tile tables failed");
   e = launch_build_tables(bs, p->d_delay, p->nchan, p->ndm, dir == 2, p->adj_pad, nullptr);
   if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
   if (e != hipSuccess) return hip_fail(e, "building tile tables");
