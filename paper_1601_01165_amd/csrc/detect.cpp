@@ -40,6 +40,13 @@ static bool det_fits(dedisp_plan p, bool u8, int vi) {
 //     32-channel, 2048-DM beam: the int32 series would be 1.64 GB), or with
 //     fewer blocks than CUs the same kernel with half the samples per tile
 //     (29 channels, 131 DM trials, 20,011 samples: 21.9 against 26.9 us).
+// What it takes is noted in the plan, so that the tables stay when others are dropped.
+static int automatic(dedisp_plan p, bool u8, int vi) {
+  std::vector<int>& ids = p->det_auto[u8];
+  if (std::find(ids.begin(), ids.end(), vi) == ids.end()) ids.push_back(vi);
+  return vi;
+}
+
 static constexpr int kDetSmallTile = 25;  // 32 DMs x 512 of the 32 DMs x 1024 of variant 23
 
 static int det_variant(dedisp_plan p, bool u8) {
@@ -48,7 +55,7 @@ static int det_variant(dedisp_plan p, bool u8) {
   if (!u8) return -1;
   static const int pref_u8[] = {23, 14, 25, 27, 16, 15, 12, 17, 18, 20, 13, 21, 19, 24, 26};
   for (int vi : pref_u8)
-    if (det_fits(p, true, vi)) return vi;
+    if (det_fits(p, true, vi)) return automatic(p, true, vi);
   return -1;
 }
 
@@ -101,10 +108,10 @@ static int f32_in_place(dedisp_plan p) {
   static const int few[] = {20, 16, 14, 18, 13, 15, 17, 39}, many[] = {42, 41, 39, 16, 14, 18, 13, 15, 17};
   if (p->nchan < kFewChannels) {
     for (int k : few)
-      if (det_fits(p, false, k)) return k;
+      if (det_fits(p, false, k)) return automatic(p, false, k);
   } else {
     for (int k : many)
-      if (det_fits(p, false, k)) return k;
+      if (det_fits(p, false, k)) return automatic(p, false, k);
   }
   return -1;
 }
@@ -118,7 +125,8 @@ static bool f32_prefers_in_place(dedisp_plan p, int nbeam, int nsamp) {
 // uint8: the small tile beside the default variant vi, or -1.  Looked at on the
 // first call whatever its size, so that later ones allocate nothing.
 static int u8_small_tile(dedisp_plan p, int vi) {
-  return vi >= 0 && vi != kDetSmallTile && p->var_det_u8 < -1 && det_fits(p, true, kDetSmallTile) ? kDetSmallTile : -1;
+  if (vi < 0 || vi == kDetSmallTile || p->var_det_u8 >= -1 || !det_fits(p, true, kDetSmallTile)) return -1;
+  return automatic(p, true, kDetSmallTile);
 }
 
 // The path of a call with a workspace of ws_bytes: a fused variant, or -1 and the

@@ -265,4 +265,5 @@ struct dedisp_plan_s {
   bool by_size[3] = {false, false, false};
   std::vector<int> fine[3];
   int var_det_f32 = -2, var_det_u8 = -2;         // single-pulse search: -1 = unfused, -2 = automatic
+  std::vector<int> det_auto[2];     // fused variants the automatic search takes (0 float32, 1 uint8)
 };

@@ -92,9 +92,11 @@ void drop_spare_tables(dedisp_plan p, int dir, int keep) {
   std::map<int, Tables>& m = dir == 0 ? p->fwd_f32 : dir == 1 ? p->fwd_u8 : p->adj_f32;
   for (auto it = m.begin(); it != m.end();) {
     const int vi = it->first;
-    const std::vector<int>& fine = p->fine[dir];
-    const bool chosen = vi == keep || (p->by_size[dir] && std::find(fine.begin(), fine.end(), vi) != fine.end()) || (dir == 0 && (vi == p->var_f32 || vi == p->var_det_f32)) ||
-                        (dir == 1 && (vi == p->var_u8 || vi == p->var_det_u8)) || (dir == 2 && vi == p->var_adj);
+    auto in = [vi](const std::vector<int>& ids) { return std::find(ids.begin(), ids.end(), vi) != ids.end(); };
+    const int det = dir == 0 ? p->var_det_f32 : p->var_det_u8;
+    const bool search = dir < 2 && (det == -2 ? in(p->det_auto[dir]) : vi == det);
+    const bool chosen = vi == keep || search || (p->by_size[dir] && in(p->fine[dir])) ||
+                        vi == (dir == 0 ? p->var_f32 : dir == 1 ? p->var_u8 : p->var_adj);
     if (chosen || it->second.pins > 0) {
       ++it;
       continue;

@@ -192,7 +192,7 @@ dedisp_status dedisp_autotune(dedisp_plan p, int32_t nbeam, int32_t nsamp, dedis
         },
         s, reps, e0, e1);
   };
-  // every variant once (its tables freed again), then the three fastest
+  // every variant once (its tables freed again unless the plan runs it), then the three fastest
   // more carefully
   std::vector<std::pair<float, int>> first;
   for (int vi = -1; vi < (int)vs.size(); ++vi) {

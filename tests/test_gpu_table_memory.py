@@ -34,3 +34,22 @@ def test_dropped_tables_are_given_back():
     assert _free() - before > 20 * MB
     batch.execute()
     torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("dtype", ["u8", "f32"])
+def test_search_tables_outlive_tuning(dtype):
+    """The automatic search keeps the tables of the variants it runs when the tuner of the forward map drops
+    what it timed: the next search allocates nothing."""
+    import paper_1601_01165_amd as dd
+
+    nc = 256 if dtype == "u8" else 64
+    plan = _plan(nc, 2048)
+    ns = 3000
+    x = dd.empty_rows(1, nc, ns + plan.max_delay, torch.uint8 if dtype == "u8" else torch.float32, "cuda", zero=True)
+    dd.detect(x, plan, nsamp=ns)
+    plan.autotune(1, ns, dtype)
+    dd.detect(x, plan, nsamp=ns)  # (torch's allocator holds the outputs and the workspace from here on)
+    plan.autotune(1, ns, dtype)
+    before = _free()
+    dd.detect(x, plan, nsamp=ns)
+    assert before - _free() < 1 * MB
