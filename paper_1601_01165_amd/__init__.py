@@ -57,7 +57,9 @@ def padded(n: int, elem_bytes: int) -> int:
 
 def empty_rows(nbeam: int, nrows: int, n: int, dtype=torch.float32, device="cuda", zero=False) -> torch.Tensor:
     """A [nbeam][nrows][n] tensor whose rows start on 16-byte boundaries."""
-    stride = padded(n, dtype.itemsize)
+    # (a Python type or None stands for what torch takes it for)
+    size = dtype.itemsize if isinstance(dtype, torch.dtype) else torch.empty((), dtype=dtype).element_size()
+    stride = padded(n, size)
     buf = (torch.zeros if zero else torch.empty)((nbeam, nrows, stride), dtype=dtype, device=device)
     return buf if stride == n else buf[:, :, :n]
 
