@@ -50,8 +50,9 @@ struct LaneTile {
       const int c = min(p * CC + cl, a.rows_in - 1);
       const float* base = in + (int64_t)c * a.in_stride + a.in_lo + a.in_shift;
       // positions outside [in_lo, in_hi) read as zero, also in a 16-byte piece
-      // that straddles in_hi (the range is checked per 4 bytes; none straddles
-      // in_lo: both it and the pieces are multiples of 16 bytes)
+      // that straddles in_hi (the range is checked per 4 bytes; tested with NaN in the
+      // rows' padding); none straddles in_lo: both it and the pieces are multiples of
+      // 16 bytes
       const __amdgpu_buffer_rsrc_t rs =
           __builtin_amdgcn_make_buffer_rsrc((void*)base, (short)0, (a.in_hi - a.in_lo) * 4, 0x00020000);
       const int u0 = t0 + sb[k] - a.in_lo;

@@ -172,8 +172,10 @@ __device__ __forceinline__ void stage_f32_async_pre(int wave, float4* lds4, cons
 
 // After the asynchronous loads of a pass have landed: rewrite the one 16-byte
 // chunk per row that straddles the end of the valid range (valid elements
-// from memory, the rest zero), whatever the hardware returned for it.  Only
-// the adjoint's range can end off a 16-byte boundary.
+// from memory, the rest zero).  The loads check the range per 4 bytes and leave
+// zeros there themselves (the lane kernels rely on it; tested with NaN in the rows'
+// padding); this keeps the window kernels right without it.  Only the adjoint's
+// range can end off a 16-byte boundary.
 template <int NWAVE, int ROWCAP>
 __device__ __forceinline__ void fix_tail_async(int wave, float4* lds4, const float* in, const TileArgs& a,
                                                const int32_t* blk, int c0, int ncc, int t0) {
