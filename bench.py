@@ -347,6 +347,30 @@ WORKLOAD_TEXT = {
 }
 
 
+def forward_kernel(variant_name, dt):
+    """Kernel that runs a forward variant of dtype dt ("direct": none fits)."""
+    if variant_name == "direct":
+        return "direct_u8_kernel" if dt == "u8" else "direct_f32_kernel"
+    if dt == "u8":
+        return variant_name.split("_")[0] + "_kernel"  # u8m, u8s, u8
+    return "lane_kernel" if variant_name.startswith("lane_") else "win_kernel"
+
+
+def search_kernels(variant_name, forward_name, dt):
+    """Kernels of a single-pulse search: a variant with the search in its epilogue, or the forward map by
+    variant forward_name and the search over the stored series."""
+    if variant_name == "unfused":
+        return forward_kernel(forward_name, dt) + " + the search over the stored series"
+    return ((variant_name.split("_")[0] + "_det_kernel") if dt == "u8" else "win_kernel") \
+        + " with the search epilogue + det_finish_kernel"
+
+
+def search_bytes(nchan, ndm, nin, elem, records):
+    """Bytes a search cannot do without: input, delay table and results, and the per-tile records where the
+    search is fused (0 where it is not: the series it stores and reads back are counted apart)."""
+    return nchan * nin * elem + 4 * nchan * ndm + records + 32 * ndm
+
+
 def measure(wl, args, steps, warmup, plain_loop=True):
     """Prepare workload wl (inputs resident in HBM), tune or pin its kernels,
     time `steps` steps after `warmup` and return the JSON line as a dict."""
@@ -441,12 +465,11 @@ def measure(wl, args, steps, warmup, plain_loop=True):
             extra["weights"] = "ones (fused multiply-add per term)"
         vi = p.variant(dt)
         variant_name = dd.variant_names(dt)[vi] if vi >= 0 else "direct"
-        kernel_name = ("direct_u8_kernel" if dt == "u8" else "direct_f32_kernel") if vi < 0 else \
-            (("u8m_kernel" if variant_name.startswith("u8m_") else "u8s_kernel" if variant_name.startswith("u8s_") else "u8_kernel")
-             if dt == "u8" else "lane_kernel" if variant_name.startswith("lane_") else "win_kernel")
+        kernel_name = forward_kernel(variant_name, dt)
     elif wl in ("detect_apertif", "detect_lofar"):
-        # single-pulse search fused into the dedispersion epilogue (boxcar
-        # widths 1..32), the unfused path (store, then search) timed beside it
+        # single-pulse search (boxcar widths 1..32), fused into the dedispersion
+        # epilogue or over stored series, whichever the tuner keeps; the unfused
+        # path (store, then search) timed beside it
         p, b, x, o = plans[0], beams[0], xs[0], outs[0]
         dt = "u8" if b.dtype == "u8" else "f32"
         # room for the unfused path too (the dedispersed rows and their records)
@@ -470,13 +493,16 @@ def measure(wl, args, steps, warmup, plain_loop=True):
             log(f"unfused (store, then search): {ms_u:.3f} ms/step")
         vi = p.detect_variant(dt)
         variant_name = dd.variant_names(dt)[vi] if vi >= 0 else "unfused"
-        # algorithmic bytes: input once, delay table, the per-tile records and the results (no series)
-        rec = dd.lib().dedisp_detect_workspace_bytes(p.handle, dd._dt(dt), 1, b.nsamp)
-        algo_bytes = b.nchan * x.shape[2] * b.elem_bytes() + 4 * b.nchan * b.ndm + rec + 32 * b.ndm
+        # the records of a fused search, 64 bytes per series and tile, fill its workspace
+        rec = dd.lib().dedisp_detect_workspace_bytes(p.handle, dd._dt(dt), 1, b.nsamp) if vi >= 0 else 0
+        algo_bytes = search_bytes(b.nchan, b.ndm, x.shape[2], b.elem_bytes(), rec)
+        if vi < 0:
+            extra["series_bytes_stored_and_read"] = 2 * 4 * b.ndm * b.nsamp
 
         def step():
             dd.detect(x, p, nsamp=b.nsamp, workspace=ws)
-        kernel_name = (("u8m_det_kernel" if variant_name.startswith("u8m_") else "u8s_det_kernel") if dt == "u8" else "win_kernel") + " with the search epilogue + det_finish_kernel"
+        fv = p.variant(dt)
+        kernel_name = search_kernels(variant_name, dd.variant_names(dt)[fv] if fv >= 0 else "direct", dt)
     else:  # diff: forward + adjoint with the weight gradient over all beams
         w = torch.ones(beams[0].nchan, device=dev)
         p0 = plans[0]
