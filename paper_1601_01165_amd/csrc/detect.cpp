@@ -95,13 +95,14 @@ static int unfused_beams(dedisp_plan p, int nbeam, int nsamp, size_t ws_bytes) {
   return (int)std::min({(size_t)nbeam, most, (ws_bytes - kUnfusedSlack) / beam});
 }
 
-// Few channels: below this many the fused search is the faster from this much
-// of series on (over 150 random calls of 8 to 160 channels it is never more than 3 %
-// behind the fused one of before, and 13 % faster on average than always unfused; 73
-// channels, 40 beams of 670 DM trials, 9995 samples: 979 and 1211 us; 16 channels, 100 DM
-// trials, 5000 samples: 22 and 11 us).
-static constexpr int kFewChannels = 96;
-static constexpr size_t kFewBytes = (size_t)16 << 20;
+// Few channels: below this many the fused search is the faster from this much of
+// series on (us, fused and unfused: 8 beams of 22 channels, 2121 DM trials, 11,614 samples 366
+// and 606; 48 channels, 4 beams of 1000 DM trials, 20,000 samples 219 and 278; 16 channels, 100 DM
+// trials, 5000 samples 22 and 11; 85 channels, 3 beams of 348 DM trials, 9591 samples 69 and 57.
+// Over 150 random calls of 8 to 160 channels 2 % slower than always unfused at most, 1.6
+// times as fast at best).
+static constexpr int kFewChannels = 64;
+static constexpr size_t kFewBytes = (size_t)32 << 20;
 
 // The variant that searches float32 beams in place, or -1.
 static int f32_in_place(dedisp_plan p) {

@@ -225,8 +225,7 @@ const std::vector<int>& default_order(int dir) {
 // times its time on regular lists, where the jump form takes 1.06 whatever the list
 // (1024 channels, 2000 DM trials, 20,000 samples: 0.95 ms in row blocks, 1.12 with the DM
 // list reversed, 1.01 slot by slot; backward, 1024 DM trials, channels in descending order:
-// 0.80, 0.97 and 0.84).  Every row was a slot's when row blocks came in, so the
-// jump form is kept for these lists.
+// 0.80, 0.97 and 0.84).  So the jump form is kept for them.
 int slots_variant(int vi) { return vi == 35 ? 49 : vi == 37 ? 50 : -1; }
 
 // The choice by size.  A plan that was not tuned keeps, beside its default
@@ -235,10 +234,9 @@ int slots_variant(int vi) { return vi == 35 ? 49 : vi == 37 ? 50 : -1; }
 //   2 us + input rows * max(alone, rounds * full) * (1 + chain * s),   rounds = ceil(blocks / CUs),
 // with us per input row measured on MI355X: `alone` with at most one block per CU (the
 // latency of a row's step), `full` a block's share of a CU that holds as many as
-// fit; s is the share of rows without a pattern.  The coarse tiles have the best
-// throughput (64 DM trials x 1280 samples: 39 adds per ns over the chip; 16 x 256 in LDS:
-// 17), the fine ones occupy the chip
-// with little work: 1024 channels, 301 DM trials, 2003 samples are 10 coarse
+// fit; s is the share of rows without a pattern, `chain` what they cost.  The coarse tiles
+// have the best throughput (64 DM trials x 1280 samples: 39 adds per ns over the chip; 16 x
+// 256 in LDS: 17), the fine ones occupy the chip with little work: 1024 channels, 301 DM trials, 2003 samples are 10 coarse
 // tiles in 473 us or 304 fine ones in 103 us, while 370 channels, 1072 DM trials,
 // 11,790 samples are 170 coarse tiles in 193 us and 315 us in fine ones.  Tiles of
 // 48 DM trials (3 waves per SIMD, 0.85 of the coarse tile's time) take the calls
@@ -248,29 +246,40 @@ int slots_variant(int vi) { return vi == 35 ? 49 : vi == 37 ? 50 : -1; }
 // in LDS; backward 93, 125 and 170).  The wide lane tiles (48) are kept where delay spans
 // leave no other lane kernel (backward, 30 channels x 102 DM trials x 2162 samples: 18.5
 // us, 61 in the default's wide windows), and the direct kernel, which stages nothing, takes
-// the calls of a few rows (12 channels, 18 DM trials, 2793 samples backward: 6.7 us, 8.6).
+// the calls of a few rows (12 channels, 18 DM trials, 2793 samples backward: 6.7 us, 8.6),
+// weighted also larger ones whose input an L2 holds (170 us, 241 in the wide lane tiles on 1294
+// channels, 16 DM trials, 464 samples; past it 247 and 168 on 883 channels, 75, 1552).
+// Weights cost the lane kernels, which apply them to each term, the factor `weights` more
+// than the others.  Over 150 random calls each way (1 to 40 beams, 8 to 1536 channels, 8
+// to 3000 DM trials, 200 to 60,000 samples; profiles/choice_by_size.txt) the time is 4 to
+// 5 % from the fastest candidate's on average, within 15 % in nine of ten, and 1.4 to 1.7
+// times at most, on few input rows: the outputs bind there, which the estimate leaves out.
 struct SizeCost {
   int vi;
-  float alone, full, chain;
+  float alone, full, chain, weights;
 };
 static constexpr int kWideLanes = 48;
 static const std::vector<SizeCost>& size_costs(int dir) {
-  static const std::vector<SizeCost> f32 = {{35, .45f, .478f, .2f},  {41, .40f, .405f, .27f}, {43, .28f, .195f, .42f},
-                                            {44, .100f, .036f, 0.f}, {45, .132f, .061f, 0.f}, {kWideLanes, .14f, .14f, 0.f}};
-  static const std::vector<SizeCost> u8 = {{22, .50f, .51f, 0.f},  {23, .27f, .207f, 0.f}, {25, .18f, .125f, 0.f},
-                                           {26, .13f, .079f, 0.f}, {27, .14f, .150f, 0.f}};
-  static const std::vector<SizeCost> adj = {{37, .45f, .478f, .2f},  {50, .47f, .440f, 0.f},
-                                            {42, .40f, .405f, .27f}, {39, .44f, .440f, 0.f},
-                                            {43, .28f, .195f, .42f}, {44, .100f, .036f, 0.f}, {46, .178f, .125f, 0.f},
-                                            {kWideLanes, .14f, .145f, 0.f}};
+  static const std::vector<SizeCost> f32 = {{35, .45f, .478f, .2f, 1.f},     {41, .40f, .405f, .27f, 1.f},
+                                            {43, .28f, .195f, .42f, 1.f},    {44, .100f, .036f, 0.f, 1.36f},
+                                            {45, .132f, .061f, 0.f, 1.16f},  {kWideLanes, .14f, .14f, 0.f, 1.24f}};
+  static const std::vector<SizeCost> u8 = {{22, .50f, .51f, 0.f, 1.f},
+                                           {23, .27f, .207f, 0.f, 1.f},
+                                           {25, .18f, .125f, 0.f, 1.f},
+                                           {26, .13f, .079f, 0.f, 1.f},
+                                           {27, .14f, .150f, 0.f, 1.f}};
+  static const std::vector<SizeCost> adj = {{37, .45f, .478f, .2f, 1.f},   {50, .47f, .440f, 0.f, 1.f},
+                                            {42, .40f, .405f, .27f, 1.f},  {39, .44f, .440f, 0.f, 1.f},
+                                            {43, .28f, .195f, .42f, 1.f},  {44, .100f, .036f, 0.f, 1.f},
+                                            {46, .178f, .125f, 0.f, 1.f},  {kWideLanes, .14f, .145f, 0.f, 1.f}};
   return dir == 1 ? u8 : dir == 2 ? adj : f32;
 }
 
 static int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
-static float size_cost(dedisp_plan p, int dir, const Variant& v, int nbeam, int64_t nout) {
+static float size_cost(dedisp_plan p, int dir, const Variant& v, int nbeam, int64_t nout, bool weighted) {
   // variants without a measured pair (wide spans): the coarse tile's rate, scaled by the tile
-  SizeCost c = {v.id, .47f, .508f * (float)(v.dt() * v.st()) / (64 * 1280), 0.f};
+  SizeCost c = {v.id, .47f, .508f * (float)(v.dt() * v.st()) / (64 * 1280), 0.f, 1.f};
   for (const SizeCost& k : size_costs(dir))
     if (k.vi == v.id) c = k;
   // the packed sums of 22 on many channels, where its stores weigh less (256 channels,
@@ -280,18 +289,21 @@ static float size_cost(dedisp_plan p, int dir, const Variant& v, int nbeam, int6
   const int64_t rows_out = dir == 2 ? p->nchan : p->ndm, rows_in = dir == 2 ? p->ndm : p->nchan;
   const int64_t blocks = ceil_div(rows_out, v.dt()) * ceil_div(nout, v.st()) * nbeam;
   const float s = c.chain > 0.f ? p->plain[dir][v.id] : 0.f;
-  return 2.f + rows_in * std::max(c.alone, (float)ceil_div(blocks, p->ncu) * c.full) * (1.f + c.chain * s);
+  return 2.f + rows_in * std::max(c.alone, (float)ceil_div(blocks, p->ncu) * c.full) * (1.f + c.chain * s) *
+                   (weighted ? c.weights : 1.f);
 }
 
-// The direct kernel's (float32): a term's latency, or with several blocks of 256 outputs per CU its share.
+// The direct kernel's (float32): a term's latency, forward longer where the input is
+// more than an L2 holds, or with several blocks of 256 outputs per CU its share.
 static float direct_cost(dedisp_plan p, int dir, int nbeam, int64_t nout) {
   const int64_t rows_out = dir == 2 ? p->nchan : p->ndm, rows_in = dir == 2 ? p->ndm : p->nchan;
   const float blocks = (float)(rows_out * ceil_div(nout, 256) * nbeam);
-  return rows_in * std::max(dir == 2 ? .233f : .13f, blocks / p->ncu * .065f);
+  const bool in_l2 = nbeam * (int64_t)p->nchan * (nout + p->max_delay) * 4 <= 6 << 20;
+  return rows_in * std::max(dir == 2 ? .233f : in_l2 ? .17f : .27f, blocks / p->ncu * .05f);
 }
 
 // The variant a call of nbeam x nout output samples runs (-1: direct).
-static int pick_variant(dedisp_plan p, int dir, int nbeam, int64_t nout) {
+static int pick_variant(dedisp_plan p, int dir, int nbeam, int64_t nout, bool weighted = false) {
   const int main = dir == 0 ? p->var_f32 : dir == 1 ? p->var_u8 : p->var_adj;
   if (!p->by_size[dir] || main < 0) return main;
   const std::vector<Variant>& vs = dir == 1 ? variants_u8() : variants_f32();
@@ -302,9 +314,9 @@ static int pick_variant(dedisp_plan p, int dir, int nbeam, int64_t nout) {
   if (dir == 1 && mv.mode == 1 && ceil_div(p->ndm, mv.dt()) * ceil_div(nout, mv.st()) * nbeam >= 16 * (int64_t)p->ncu)
     return main;
   int best = main;
-  float least = size_cost(p, dir, mv, nbeam, nout);
+  float least = size_cost(p, dir, mv, nbeam, nout, weighted);
   for (int vi : p->fine[dir]) {
-    const float c = size_cost(p, dir, vs[vi], nbeam, nout);
+    const float c = size_cost(p, dir, vs[vi], nbeam, nout, weighted);
     if (c < least) {
       least = c;
       best = vi;
@@ -673,7 +685,7 @@ dedisp_status dedisp_execute(dedisp_plan p, int32_t nbeam, int32_t nsamp, const 
     return fail(DEDISP_E_ALIGN, "pointers and row byte sizes must be multiples of 16 bytes");
   hipStream_t s = (hipStream_t)stream;
   ensure_chosen(p, u8 ? 1 : 0);
-  const int vi = pick_variant(p, u8 ? 1 : 0, nbeam, nsamp);
+  const int vi = pick_variant(p, u8 ? 1 : 0, nbeam, nsamp, d_w != nullptr);
   hipError_t e;
   if (vi < 0) {
     if (u8)
