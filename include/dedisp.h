@@ -264,12 +264,14 @@ dedisp_status dedisp_batch_destroy(dedisp_batch batch);
  *   S/N_w     = (max_t B_w(t) - w * mean) / (std * sqrt(w)), 0 when std == 0
  * and the result is the width with the largest S/N (ties: the narrower), the
  * first t where that width's boxcar reaches its maximum, the S/N, mean and
- * std.  The series themselves are never written to memory: the search runs
- * in the epilogue of the dedispersion tile kernel (time tiles overlap by the
- * widest window, so each window lies inside one tile), which leaves one
- * 64-byte record per (series, tile) in the workspace; a second kernel merges
- * them.  uint8 input is searched in exact integers (float32 input: boxcar
- * sums in FP32 by pairwise doubling); moments and S/N are FP64.
+ * std.  Two paths give it.  Fused: the search runs in the epilogue of the
+ * dedispersion tile kernel (time tiles overlap by the widest window, so each
+ * window lies inside one tile), the series are never written to memory, each
+ * (series, tile) leaves one 64-byte record in the workspace, and a second kernel
+ * merges them; uint8 input is searched in exact integers.  Unfused: the series
+ * of some beams are stored in the workspace (float32, or int32 for uint8 input)
+ * and searched there in float32 (dedisp_detect_rows).  float32 boxcar sums go by
+ * pairwise doubling; moments and S/N are FP64.
  *   d_in, in_type, in_stride, d_w: as for dedisp_execute
  *   d_snr    [nbeam][ndm] double        d_width [nbeam][ndm] int32
  *   d_start  [nbeam][ndm] int32         d_mean, d_std [nbeam][ndm] double, or NULL
@@ -301,8 +303,11 @@ dedisp_status dedisp_detect(dedisp_plan plan, int32_t nbeam, int32_t nsamp, cons
  * (0 for invalid arguments).  May build tile tables. */
 size_t dedisp_detect_workspace_bytes(dedisp_plan plan, dedisp_dtype in_type, int32_t nbeam, int32_t nsamp);
 
-/* The variant dedisp_detect would use for in_type (an index of
- * dedisp_variant_name(in_type, .)), or -1 for the unfused path. */
+/* The search path set or tuned for in_type, else the default one: a variant with
+ * the search in its epilogue (an index of dedisp_variant_name(in_type, .)), or -1
+ * for the unfused path.  Unless one was set or tuned, a call may take another by
+ * its size: float32 the fused search in place of -1 (see dedisp_detect), uint8
+ * smaller tiles with fewer blocks than CUs. */
 int32_t dedisp_detect_variant(dedisp_plan plan, dedisp_dtype in_type);
 
 /* Force the search path for in_type: a variant with the search in its

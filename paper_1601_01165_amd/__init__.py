@@ -154,8 +154,9 @@ class Plan:
         return int(lib().dedisp_plan_adjoint_variant(self._h))
 
     def detect_variant(self, dtype="f32") -> int:
-        """Variant with the single-pulse search in its epilogue that detect
-        uses for dtype (-1: the unfused path)."""
+        """Variant with the single-pulse search in its epilogue that is set, tuned
+        or the default for dtype (-1: the unfused path); untuned calls may take
+        another by their size."""
         return int(lib().dedisp_detect_variant(self.handle, _dt(dtype)))
 
     def autotune_adjoint(self, nbeam: int, nsamp: int) -> dict:
@@ -307,10 +308,14 @@ def _det_outputs(shape, device):
 
 def detect(x: torch.Tensor, plan: Plan, nsamp: int | None = None, w: torch.Tensor | None = None, nwidth: int = 6,
            workspace: torch.Tensor | None = None) -> dict:
-    """Single-pulse search over every dedispersed series without storing the
-    series: boxcars of widths 1, 2, ..., 2^(nwidth-1); returns tensors
-    [nbeam][ndm] (or [ndm] for 2-D input): snr (f64), width, start (i32),
-    mean, std (f64).  See dedisp_detect in include/dedisp.h."""
+    """Single-pulse search over every dedispersed series: boxcars of widths 1, 2,
+    ..., 2^(nwidth-1); returns tensors [nbeam][ndm] (or [ndm] for 2-D input): snr
+    (f64), width, start (i32), mean, std (f64).  uint8 input, and large float32
+    calls of few channels, are searched as they are dedispersed; other float32
+    series are stored in the workspace first, those of at most 1 GiB of beams
+    at a time.  workspace: scratch to reuse between calls (one sized for the
+    longest call serves every shorter one); another is allocated where none is
+    given or it is too small.  See dedisp_detect in include/dedisp.h."""
     squeeze = x.dim() == 2
     xr = _as_rows(x)
     nb, nc, nin = xr.shape
