@@ -288,7 +288,8 @@ static float size_cost(dedisp_plan p, int dir, const Variant& v, int nbeam, int6
   if (dir == 1 && v.id == 22 && p->nchan >= 48) c.full = .385f;
   const int64_t rows_out = dir == 2 ? p->nchan : p->ndm, rows_in = dir == 2 ? p->ndm : p->nchan;
   const int64_t blocks = ceil_div(rows_out, v.dt()) * ceil_div(nout, v.st()) * nbeam;
-  const float s = c.chain > 0.f ? p->plain[dir][v.id] : 0.f;
+  const auto plain = p->plain[dir].find(v.id);  // (known for every variant the choice can take)
+  const float s = c.chain > 0.f && plain != p->plain[dir].end() ? plain->second : 0.f;
   return 2.f + rows_in * std::max(c.alone, (float)ceil_div(blocks, p->ncu) * c.full) * (1.f + c.chain * s) *
                    (weighted ? c.weights : 1.f);
 }
