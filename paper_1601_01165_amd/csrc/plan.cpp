@@ -231,10 +231,12 @@ int slots_variant(int vi) { return vi == 35 ? 49 : vi == 37 ? 50 : -1; }
 // The choice by size.  A plan that was not tuned keeps, beside its default
 // variant, a few with smaller tiles, and each call takes the one with the least
 // estimated time,
-//   2 us + input rows * max(alone, rounds * full) * (1 + chain * s),   rounds = ceil(blocks / CUs),
-// with us per input row measured on MI355X: `alone` with at most one block per CU (the
-// latency of a row's step), `full` a block's share of a CU that holds as many as
-// fit; s is the share of rows without a pattern, `chain` what they cost.  The coarse tiles
+//   max(start + rows * alone * f, rounds * (turn + rows * full * f)),   rounds = ceil(blocks / CUs),
+//   f = 1 + chain * s, with weights also times `weights`,
+// in us, rows the input rows, fitted to about 2000 random calls on MI355X: start and `alone` with at
+// most one block per CU (the latency of a row's step), turn and `full` a block's share of a CU that holds as many as
+// fit (turn: the tile's prologue and outputs, which with one block per CU nothing hides, and in the
+// adjoint its partial sums); s is the share of rows without a pattern, `chain` what they cost.  The coarse tiles
 // have the best throughput (64 DM trials x 1280 samples: 39 adds per ns over the chip; 16 x
 // 256 in LDS: 17), the fine ones occupy the chip with little work: 1024 channels, 301 DM trials, 2003 samples are 10 coarse
 // tiles in 473 us or 304 fine ones in 103 us, while 370 channels, 1072 DM trials,
@@ -243,7 +245,11 @@ int slots_variant(int vi) { return vi == 35 ? 49 : vi == 37 ? 50 : -1; }
 // that would leave the last round of coarse tiles half empty, and tiles of 32 x
 // 768 those between the sizes (two blocks per CU share one's waits: 2 beams of 264
 // channels, 239 DM trials, 18,314 samples take 106 us, 132 us in coarse tiles and 153
-// in LDS; backward 93, 125 and 170).  The wide lane tiles (48) are kept where delay spans
+// in LDS; backward 93, 125 and 170).  Beside the wide windows (39, 40: 8 to 12 samples between
+// neighbouring rows) also 16 x 768 samples in a window of 48 (11) and, forward, 16 x 512 (46) are
+// kept, whose blocks share a CU: 8 beams of 20 channels, 256 DM trials, 27,155 samples
+// take 122 us in 39 and 86 in 11, while 3 of 592 channels, 605 DM trials, 15,894 samples take
+// 663 and 1094.  The wide lane tiles (48) are kept where delay spans
 // leave no other lane kernel (backward, 30 channels x 102 DM trials x 2162 samples: 18.5
 // us, 61 in the default's wide windows), and the direct kernel, which stages nothing, takes
 // the calls of a few rows (12 channels, 18 DM trials, 2793 samples backward: 6.7 us, 8.6),
@@ -251,56 +257,73 @@ int slots_variant(int vi) { return vi == 35 ? 49 : vi == 37 ? 50 : -1; }
 // channels, 16 DM trials, 464 samples; past it 247 and 168 on 883 channels, 75, 1552).
 // Weights cost the lane kernels, which apply them to each term, the factor `weights` more
 // than the others.  Over 150 random calls each way (1 to 40 beams, 8 to 1536 channels, 8
-// to 3000 DM trials, 200 to 60,000 samples; profiles/choice_by_size.txt) the time is 4 to
-// 5 % from the fastest candidate's on average, within 15 % in nine of ten, and 1.4 to 1.7
-// times at most, on few input rows: the outputs bind there, which the estimate leaves out.
+// to 3000 DM trials, 200 to 60,000 samples; profiles/choice_by_size.txt) the time is 2 to 3 %
+// from the fastest kernel's on average (uint8 5 %), within 15 % in nine of ten, and 1.4 to 1.6 times at
+// most, where the input rows are few or the gradient's rows shorter than the delays.
 struct SizeCost {
   int vi;
-  float alone, full, chain, weights;
+  float start, alone, turn, full, chain, weights;
+  enum { any_plan, wide_plan, if_default } kept = any_plan;  // beside which defaults it is kept
 };
 static constexpr int kWideLanes = 48;
 static const std::vector<SizeCost>& size_costs(int dir) {
-  static const std::vector<SizeCost> f32 = {{35, .45f, .478f, .2f, 1.f},     {41, .40f, .405f, .27f, 1.f},
-                                            {43, .28f, .195f, .42f, 1.f},    {44, .100f, .036f, 0.f, 1.36f},
-                                            {45, .132f, .061f, 0.f, 1.16f},  {kWideLanes, .14f, .14f, 0.f, 1.24f}};
-  static const std::vector<SizeCost> u8 = {{22, .50f, .51f, 0.f, 1.f},
-                                           {23, .27f, .207f, 0.f, 1.f},
-                                           {25, .18f, .125f, 0.f, 1.f},
-                                           {26, .13f, .079f, 0.f, 1.f},
-                                           {27, .14f, .150f, 0.f, 1.f}};
-  static const std::vector<SizeCost> adj = {{37, .45f, .478f, .2f, 1.f},   {50, .47f, .440f, 0.f, 1.f},
-                                            {42, .40f, .405f, .27f, 1.f},  {39, .44f, .440f, 0.f, 1.f},
-                                            {43, .28f, .195f, .42f, 1.f},  {44, .100f, .036f, 0.f, 1.f},
-                                            {46, .178f, .125f, 0.f, 1.f},  {kWideLanes, .14f, .145f, 0.f, 1.f}};
+  constexpr auto wide = SizeCost::wide_plan;
+  constexpr auto main = SizeCost::if_default;
+  static const std::vector<SizeCost> f32 = {{35, 9.3f, .441f, 21.f, .478f, .2f, 1.f},
+                                            {49, 9.8f, .460f, 21.f, .500f, 0.f, 1.f, main},
+                                            {39, 7.9f, .414f, 17.f, .450f, 0.f, 1.f, main},
+                                            {40, 5.4f, .509f, 5.0f, .220f, 0.f, 1.f, main},
+                                            {41, 8.3f, .400f, 16.2f, .420f, .27f, 1.f},
+                                            {43, 5.0f, .286f, 5.3f, .181f, .5f, 1.f},
+                                            {44, 2.9f, .074f, 1.0f, .037f, 0.f, 1.36f},
+                                            {45, 3.0f, .113f, 1.0f, .0625f, 0.f, 1.16f},
+                                            {46, 3.1f, .163f, 1.5f, .126f, 0.f, 1.f, wide},
+                                            {11, 3.3f, .347f, 1.7f, .150f, 0.f, 1.f, wide},
+                                            {kWideLanes, 2.8f, .126f, 1.6f, .136f, 0.f, 1.24f}};
+  // (two rounds of 23 are one of 22: on few channels they cost less, where the 8 us that do not
+  // grow with the channels weigh most, on many more: 256 channels, 2048 DM trials, 60,000
+  // samples take 0.735 ms in 22 and 0.761 in 23)
+  static const std::vector<SizeCost> u8 = {{22, 5.5f, .456f, 8.0f, .357f, 0.f, 1.f},
+                                           {23, 4.6f, .268f, 3.9f, .200f, 0.f, 1.f},
+                                           {25, 3.7f, .180f, 2.2f, .122f, 0.f, 1.f},
+                                           {26, 3.4f, .127f, 1.4f, .080f, 0.f, 1.f},
+                                           {27, 3.6f, .132f, 2.1f, .138f, 0.f, 1.f}};
+  static const std::vector<SizeCost> adj = {{37, 22.7f, .465f, 50.f, .485f, .2f, 1.f},
+                                            {50, 22.9f, .489f, 50.f, .510f, 0.f, 1.f, main},
+                                            {42, 19.6f, .425f, 33.f, .428f, .27f, 1.f},
+                                            {39, 17.9f, .452f, 36.f, .470f, 0.f, 1.f},
+                                            {40, 13.7f, .599f, 15.f, .215f, 0.f, 1.f, main},
+                                            {43, 13.1f, .283f, 10.f, .190f, .42f, 1.f},
+                                            {44, 6.1f, .0735f, 2.3f, .0355f, 0.f, 1.f},
+                                            {46, 8.3f, .172f, 5.8f, .127f, 0.f, 1.f},
+                                            {11, 9.7f, .400f, 9.2f, .130f, 0.f, 1.f, wide},
+                                            {kWideLanes, 7.1f, .125f, 5.9f, .135f, 0.f, 1.f}};
   return dir == 1 ? u8 : dir == 2 ? adj : f32;
 }
 
 static int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
 static float size_cost(dedisp_plan p, int dir, const Variant& v, int nbeam, int64_t nout, bool weighted) {
-  // variants without a measured pair (wide spans): the coarse tile's rate, scaled by the tile
-  SizeCost c = {v.id, .47f, .508f * (float)(v.dt() * v.st()) / (64 * 1280), 0.f, 1.f};
+  // variants that were not measured (wide spans): the coarse tile's rate, scaled by the tile
+  SizeCost c = {v.id, 2.f, .47f, 2.f, .508f * (float)(v.dt() * v.st()) / (64 * 1280), 0.f, 1.f};
   for (const SizeCost& k : size_costs(dir))
     if (k.vi == v.id) c = k;
-  // the packed sums of 22 on many channels, where its stores weigh less (256 channels,
-  // 2048 DM trials, 60,000 samples: 0.735 ms, 0.761 on the matrix cores; of 235 random
-  // calls 17 were up to 10 % slower on the kernel chosen without this than on 22, one 2 % with it)
-  if (dir == 1 && v.id == 22 && p->nchan >= 48) c.full = .385f;
   const int64_t rows_out = dir == 2 ? p->nchan : p->ndm, rows_in = dir == 2 ? p->ndm : p->nchan;
-  const int64_t blocks = ceil_div(rows_out, v.dt()) * ceil_div(nout, v.st()) * nbeam;
+  const float rounds = (float)ceil_div(ceil_div(rows_out, v.dt()) * ceil_div(nout, v.st()) * nbeam, p->ncu);
   const auto plain = p->plain[dir].find(v.id);  // (known for every variant the choice can take)
   const float s = c.chain > 0.f && plain != p->plain[dir].end() ? plain->second : 0.f;
-  return 2.f + rows_in * std::max(c.alone, (float)ceil_div(blocks, p->ncu) * c.full) * (1.f + c.chain * s) *
-                   (weighted ? c.weights : 1.f);
+  const float rows = rows_in * (1.f + c.chain * s) * (weighted ? c.weights : 1.f);
+  return std::max(c.start + rows * c.alone, rounds * (c.turn + rows * c.full));
 }
 
 // The direct kernel's (float32): a term's latency, forward longer where the input is
-// more than an L2 holds, or with several blocks of 256 outputs per CU its share.
+// more than an L2 holds, or with several blocks of 256 outputs per CU its share; the
+// adjoint's partial sums beside it.
 static float direct_cost(dedisp_plan p, int dir, int nbeam, int64_t nout) {
   const int64_t rows_out = dir == 2 ? p->nchan : p->ndm, rows_in = dir == 2 ? p->ndm : p->nchan;
   const float blocks = (float)(rows_out * ceil_div(nout, 256) * nbeam);
   const bool in_l2 = nbeam * (int64_t)p->nchan * (nout + p->max_delay) * 4 <= 6 << 20;
-  return rows_in * std::max(dir == 2 ? .233f : in_l2 ? .17f : .27f, blocks / p->ncu * .05f);
+  return (dir == 2 ? 5.f : 0.f) + rows_in * std::max(dir == 2 ? .2f : in_l2 ? .17f : .27f, blocks / p->ncu * .05f);
 }
 
 // The variant a call of nbeam x nout output samples runs (-1: direct).
@@ -355,9 +378,12 @@ static void ensure_chosen(dedisp_plan p, int dir) {
   v = first;
   if (first < 0) return;
   std::vector<int> build = {first};
-  bool lanes = false;  // a lane kernel fits
+  const bool wide = first == 39 || first == 40;  // the wide windows
+  bool lanes = false;                            // a lane kernel fits
   auto wanted = [&](const SizeCost& c) {
-    if (c.vi == first || c.vi == blocks || c.vi == slots || p->fits[dir][c.vi] != 0 || (c.vi == kWideLanes && lanes && dir != 1)) return false;
+    if (c.vi == first || c.vi == blocks || c.vi == slots || c.kept == SizeCost::if_default ||
+        (c.kept == SizeCost::wide_plan && !wide) || p->fits[dir][c.vi] != 0 || (c.vi == kWideLanes && lanes && dir != 1))
+      return false;
     lanes |= dir != 1 && variants_f32()[c.vi].kind == KIND_LANE_F32;
     return true;
   };
