@@ -99,8 +99,11 @@ static int unfused_beams(dedisp_plan p, int nbeam, int nsamp, size_t ws_bytes) {
 // series on (us, fused and unfused: 8 beams of 22 channels, 2121 DM trials, 11,614 samples 366
 // and 606; 48 channels, 4 beams of 1000 DM trials, 20,000 samples 219 and 278; 16 channels, 100 DM
 // trials, 5000 samples 22 and 11; 85 channels, 3 beams of 348 DM trials, 9591 samples 69 and 57.
-// Over 150 random calls of 8 to 160 channels 2 % slower than always unfused at most, 1.6
-// times as fast at best).
+// Over 108 random calls of 8 to 63 channels, 4 to 300 DM trials 1.1 times as fast as unfused
+// on average, 0.84 to 1.6).  Tiles of more than 16 DM trials (delay spans too wide for the
+// first of `few`) need two of them for that: 39's 48 leave most of their waves without work on
+// 12 DM trials (40 beams of 45 channels, 53,352 samples: 254 us, 137 unfused), and are
+// 0.78 to 0.99 times as fast up to 79 DM trials, 0.91 to 1.25 from 97.
 static constexpr int kFewChannels = 64;
 static constexpr size_t kFewBytes = (size_t)32 << 20;
 
@@ -120,7 +123,12 @@ static int f32_in_place(dedisp_plan p) {
 // Whether float32 calls of these sizes go in place if they can.
 static bool f32_prefers_in_place(dedisp_plan p, int nbeam, int nsamp) {
   const size_t beam = beam_series(p, nsamp);
-  return beam > kUnfusedBytes || (p->nchan < kFewChannels && nbeam * beam > kFewBytes);
+  if (beam > kUnfusedBytes) return true;
+  if (p->nchan >= kFewChannels || nbeam * beam <= kFewBytes) return false;
+  const int k = f32_in_place(p);
+  if (k < 0) return false;
+  const int dt = variants_f32()[k].dt();
+  return dt <= 16 || p->ndm >= 2 * dt;
 }
 
 // uint8: the small tile beside the default variant vi, or -1.  Looked at on the

@@ -118,3 +118,19 @@ def test_autotune_times_every_fused_variant_of_a_large_call():
     assert len(fit) > 10
     times = plan.autotune_detect(512, 16000, "u8")
     assert set(times) == fit | {"unfused"}
+
+
+@pytest.mark.parametrize("nd", [12, 49, 97])
+def test_f32_few_channels_few_dms(nd):
+    """Spans of 10 samples between trials, which only tiles of 48 DM trials take: fewer than two of them are
+    stored and searched, more searched in place; both give the same."""
+    dd = _dd()
+    f = 1270.0 + (np.arange(45) + 0.5) * 300.0 / 45
+    dms = np.arange(nd) * 0.6
+    plan, plain = dd.Plan(f, 50e-6, dms), dd.Plan(f, 50e-6, dms)
+    ns = 9000000 // nd  # 36 MB of series
+    x = dd.empty_rows(1, 45, ns + plan.max_delay, torch.float32, "cuda")
+    x.copy_(torch.randint(-3, 4, x.shape, device="cuda"))
+    plain.set_detect_variant(-1)
+    for n in (ns, ns // 3):
+        _same(dd.detect(x, plan, nsamp=n), dd.detect(x, plain, nsamp=n))
