@@ -340,10 +340,8 @@ WORKLOAD_TEXT = {
     "apertif": "Apertif-like beam: 1024 ch 1270-1570 MHz, 2048 DMs step 0.25, 20000 samples, FP32",
     "lofar": "LOFAR-like beam: 32 ch 134.875-141.125 MHz, 2048 DMs step 0.01, 200000 samples, u8->i32",
     "diff": "32 Apertif-like beams, 1024 ch, 1024 DMs, 20000 samples: forward + adjoint + grad_w",
-    "detect_apertif": "Apertif-like beam (as apertif) dedispersed and searched with boxcars of 1..32 "
-                      "samples in one pass, series never stored",
-    "detect_lofar": "LOFAR-like beam (as lofar) dedispersed and searched with boxcars of 1..32 "
-                    "samples in one pass, series never stored",
+    "detect_apertif": "Apertif-like beam (as apertif) dedispersed and searched with boxcars of 1..32 samples",
+    "detect_lofar": "LOFAR-like beam (as lofar) dedispersed and searched with boxcars of 1..32 samples",
 }
 
 
