@@ -255,8 +255,8 @@ int slots_variant(int vi) { return vi == 35 ? 49 : vi == 37 ? 50 : -1; }
 // the calls of a few rows (12 channels, 18 DM trials, 2793 samples backward: 6.7 us, 8.6),
 // weighted also larger ones whose input an L2 holds (170 us, 241 in the wide lane tiles on 1294
 // channels, 16 DM trials, 464 samples; past it 247 and 168 on 883 channels, 75, 1552).
-// Weights cost the lane kernels, which apply them to each term, the factor `weights` more
-// than the others.  Over 150 random calls each way (1 to 40 beams, 8 to 1536 channels, 8
+// Weights cost the lane kernels, which apply them to each term, and a little the smaller row
+// blocks the factor `weights` more than the others.  Over 150 random calls each way (1 to 40 beams, 8 to 1536 channels, 8
 // to 3000 DM trials, 200 to 60,000 samples; profiles/choice_by_size.txt) the time is 2 to 3 %
 // from the fastest kernel's on average (uint8 5 %), within 15 % in nine of ten, and 1.4 to 1.6 times at
 // most, where the input rows are few or the gradient's rows shorter than the delays.
@@ -269,12 +269,12 @@ static constexpr int kWideLanes = 48;
 static const std::vector<SizeCost>& size_costs(int dir) {
   constexpr auto wide = SizeCost::wide_plan;
   constexpr auto main = SizeCost::if_default;
-  static const std::vector<SizeCost> f32 = {{35, 9.3f, .441f, 21.f, .478f, .2f, 1.f},
+  static const std::vector<SizeCost> f32 = {{35, 9.3f, .441f, 21.f, .478f, .25f, 1.f},
                                             {49, 9.8f, .460f, 21.f, .500f, 0.f, 1.f, main},
                                             {39, 7.9f, .414f, 17.f, .450f, 0.f, 1.f, main},
                                             {40, 5.4f, .509f, 5.0f, .220f, 0.f, 1.f, main},
-                                            {41, 8.3f, .400f, 16.2f, .420f, .27f, 1.f},
-                                            {43, 5.0f, .286f, 5.3f, .181f, .5f, 1.f},
+                                            {41, 8.3f, .400f, 16.2f, .420f, .32f, 1.07f},
+                                            {43, 5.0f, .286f, 5.3f, .181f, .45f, 1.08f},
                                             {44, 2.9f, .074f, 1.0f, .037f, 0.f, 1.36f},
                                             {45, 3.0f, .113f, 1.0f, .0625f, 0.f, 1.16f},
                                             {46, 3.1f, .163f, 1.5f, .126f, 0.f, 1.f, wide},
